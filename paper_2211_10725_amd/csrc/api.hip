@@ -203,8 +203,10 @@ DwPlan dw_plan(const snn_layer_desc *d) {
     mn.a_dtype = d->grad_dtype; mn.a_kc = false; mn.lda = d->n_out;
     mn.b_dtype = d->in_dtype; mn.b_kc = false; mn.ldb = d->n_in;
     mn.allow_split = split_ok(d);
-    const bool async_mn = gemm_async_applies(mn);
-    p.planes = async_mn && d->grad_dtype == SNN_F32;
+    const bool async_mn = gemm_async_applies(mn) ||
+                          (gemm_joint_applies(mn) && (mn_direct || d->n_out % 8 == 0));
+    // (the scan's planes have dL/dI's own rows: whole 16-byte chunks)
+    p.planes = async_mn && d->grad_dtype == SNN_F32 && d->n_out % 8 == 0;
     p.transposed = split_ok(d) && gemm16_applies(kc) && d->n_out > 16 && !mn_direct && !async_mn &&
                    2.0 * M * d->n_in * d->n_out >= kTransposeFlops;
     if (p.transposed) {
@@ -237,6 +239,7 @@ size_t layer_planes_bytes(const snn_layer_desc *d) { return dcur_t_planes(d) ? d
 
 struct DxPlan {
     bool transposed;
+    bool joint;  // fp32 dI x fp32 W from their parts, both in their own layouts
     size_t wt_bytes;  // W^T
     size_t gemm_bytes;
 };
@@ -248,8 +251,19 @@ DxPlan dx_plan(const snn_layer_desc *d) {
     kc.M = M; kc.N = d->n_in; kc.K = d->n_out;
     kc.a_dtype = d->grad_dtype; kc.a_kc = true;
     kc.b_dtype = d->w_dtype; kc.b_kc = true;
+    GemmArgs own{};
+    own.M = M; own.N = d->n_in; own.K = d->n_out;
+    own.a_dtype = d->grad_dtype; own.a_kc = true; own.lda = d->n_out;
+    own.b_dtype = d->w_dtype; own.b_kc = false; own.ldb = d->n_in;
+    own.allow_split = split_ok(d);
+    kc.lda = kc.ldb = d->n_out;
+    kc.allow_split = split_ok(d);
+    // the joint kernel reads both operands as they are (16-bit pairs: unless
+    // 256 x 256 tiles fill the device)
+    const bool own_layout = gemm_joint_applies(own) && !gemm_async_applies(kc);
+    p.joint = own_layout && d->grad_dtype == SNN_F32 && d->w_dtype == SNN_F32;
     // a layer with few outputs (short contraction) reads W in its own layout
-    p.transposed = split_ok(d) && gemm16_applies(kc) && d->n_out > 16 &&
+    p.transposed = !own_layout && split_ok(d) && gemm16_applies(kc) && d->n_out > 16 &&
                    2.0 * M * d->n_in * d->n_out >= kTransposeFlops;
     if (p.transposed) {
         p.wt_bytes = align_up((size_t)d->n_in * d->n_out * dtype_bytes(d->w_dtype));
@@ -530,18 +544,25 @@ snn_status snn_neuron_bwd(const snn_layer_desc *d, const snn_grad_in *grad, cons
     return hip_status(e);
 }
 
-snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void *dcur_t,
-                           const float *dcur_scale, const uint8_t *pool_arg, const void *x,
-                           const void *w, float *grad_w, float *grad_x, void *ws,
-                           size_t ws_bytes, hipStream_t stream) {
-    snn_status st = check_desc(d);
-    if (st != SNN_OK) return st;
-    if (d->synapse == SNN_SYN_NONE) return SNN_ERR_UNSUPPORTED;
+}  // extern "C"
+
+namespace {
+// dL/dI as the reverse scan's bf16 planes serves the input gradient too where
+// that contracts parts
+bool dx_from_planes(const snn_layer_desc *d) { return dcur_t_planes(d) && dx_plan(d).joint; }
+
+// snn_synapse_bwd; the layer call passes no row-major dcur where every
+// requested gradient reads dcur_t
+snn_status synapse_bwd(const snn_layer_desc *d, const void *dcur, const void *dcur_t,
+                       const float *dcur_scale, const uint8_t *pool_arg, const void *x,
+                       const void *w, float *grad_w, float *grad_x, void *ws,
+                       size_t ws_bytes, hipStream_t stream) {
     // dcur_t (the transposed weight-gradient operand) serves the weight
     // gradient when the layer's plan contracts it; dcur everything else
     const bool use_t = dcur_t && grad_w && dcur_t_bytes(d) > 0;
     if (dcur_t && !aligned16(dcur_t)) return SNN_ERR_ALIGN;
-    if (!dcur && (grad_x || (grad_w && !use_t))) return SNN_ERR_NULL;
+    const bool dx_t = dcur_t && grad_x && dx_from_planes(d);
+    if (!dcur && ((grad_x && !dx_t) || (grad_w && !use_t))) return SNN_ERR_NULL;
     if (!dcur && !dcur_t) return SNN_ERR_NULL;
     if (scaled_grad(d)) {
         if (!dcur_scale) return SNN_ERR_NULL;
@@ -618,6 +639,11 @@ snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void
         GemmArgs g{};
         g.M = M; g.N = d->n_in; g.K = d->n_out;
         g.A = dcur; g.lda = d->n_out; g.a_dtype = d->grad_dtype; g.a_kc = true;
+        if (dx_t) {
+            g.A = dcur_t;
+            g.a_dtype = kPlanes3;
+            g.a_ps = (int64_t)M * d->n_out;
+        }
         g.C = grad_x; g.ldc = d->n_in; g.bias = nullptr; g.allow_split = split_ok(d);
         g.c_div = dcur_scale;
         hipError_t e;
@@ -634,6 +660,22 @@ snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void
         if (e != hipSuccess) return SNN_ERR_HIP;
     }
     return SNN_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void *dcur_t,
+                           const float *dcur_scale, const uint8_t *pool_arg, const void *x,
+                           const void *w, float *grad_w, float *grad_x, void *ws,
+                           size_t ws_bytes, hipStream_t stream) {
+    snn_status st = check_desc(d);
+    if (st != SNN_OK) return st;
+    if (d->synapse == SNN_SYN_NONE) return SNN_ERR_UNSUPPORTED;
+    if (!dcur && grad_x && (!dcur_t || aligned16(dcur_t))) return SNN_ERR_NULL;
+    return synapse_bwd(d, dcur, dcur_t, dcur_scale, pool_arg, x, w, grad_w, grad_x, ws, ws_bytes,
+                       stream);
 }
 
 snn_status snn_layer_fwd(const snn_layer_desc *d, const void *x, const void *w,
@@ -699,12 +741,12 @@ snn_status snn_layer_bwd(const snn_layer_desc *d, const snn_grad_in *grad, const
     // transpose, so the layer call keeps the transpose.  Where it takes an
     // fp32 dL/dI in its own layout, the scan writes the three bf16 planes
     // (coalesced like dL/dI itself) instead of the fp32 values, which only
-    // the input gradient still needs.
+    // an input gradient that does not contract the planes itself still needs.
     void *dcur_t = nullptr;
     void *dcur_rm = dcur;
     if (grad_w && layer_planes_bytes(d) > 0) {
         dcur_t = planes;
-        if (!grad_x) dcur_rm = nullptr;
+        if (!grad_x || dx_from_planes(d)) dcur_rm = nullptr;
     }
     st = snn_neuron_bwd(d, grad, v, cur, ckpt, dcur_rm, dcur_t, scale, grad_b, grad_v, colsum,
                         neuron_ws(d), stream);
@@ -712,8 +754,8 @@ snn_status snn_layer_bwd(const snn_layer_desc *d, const snn_grad_in *grad, const
     if (!grad_w && !grad_x) return SNN_OK;
     const uint8_t *arg = nullptr;
     if (d->synapse == SNN_SYN_CONV5_POOL2) arg = reinterpret_cast<const uint8_t *>(sb + l.pool_offset);
-    return snn_synapse_bwd(d, dcur_rm, dcur_t, scale, arg, x, w, grad_w, grad_x, gws,
-                           bwd_gemm_ws(d), stream);
+    return synapse_bwd(d, dcur_rm, dcur_t, scale, arg, x, w, grad_w, grad_x, gws, bwd_gemm_ws(d),
+                       stream);
 }
 
 size_t snn_loss_workspace_bytes(int32_t kind, int32_t B, int32_t K) {

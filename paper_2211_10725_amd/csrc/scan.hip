@@ -467,14 +467,17 @@ __global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
                 }
                 if (dcur) store_grad<GT, VEC>(dcur, (int64_t)t * C + col, d, scale);
                 if constexpr (TRM == TR_PLANES) {
+                    uint32_t part[3][VEC];
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+                        split_bf16x3(d[v], part[0][v], part[1][v], part[2][v]);
 #pragma unroll
                     for (int p = 0; p < 3; ++p) {
                         uint16_t *q = dcur_t + p * t_plane + (int64_t)t * C + col;
-                        const uint32_t h0 = grad_part<SNN_F32>(d[0], p, 1.f);
                         if constexpr (VEC == 2)
-                            *reinterpret_cast<uint32_t *>(q) = h0 | (grad_part<SNN_F32>(d[1], p, 1.f) << 16);
+                            *reinterpret_cast<uint32_t *>(q) = part[p][0] | (part[p][1] << 16);
                         else
-                            q[0] = (uint16_t)h0;
+                            q[0] = (uint16_t)part[p][0];
                     }
                 }
                 if constexpr (TR) {

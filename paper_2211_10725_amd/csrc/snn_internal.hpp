@@ -41,6 +41,25 @@ inline size_t dtype_bytes(int dt) {
     }
 }
 
+// The exact split of an fp32 value into three bf16 parts x = hi + mid + lo (bit
+// patterns): hi = bf16(x) (nearest even), mid = bf16(x - hi), lo = x - hi -
+// mid; each subtraction is exact.  A finite x that would round to infinity
+// is truncated instead; an infinity or NaN is hi alone.
+__device__ inline uint32_t bf16_rne_u32(float x) {
+    const uint32_t b = __float_as_uint(x);
+    return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
+}
+__device__ inline void split_bf16x3(float x, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    const uint32_t b = __float_as_uint(x);
+    hi = (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
+    const bool top = (b & 0x7fffffffu) >= 0x7f7f8000u;  // rounds to infinity, or not finite
+    const bool special = (b & 0x7f800000u) == 0x7f800000u;
+    if (top) hi = (b >> 16) | ((b & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u);
+    const float r = special ? 0.f : x - __uint_as_float(hi << 16);
+    mid = bf16_rne_u32(r);
+    lo = bf16_rne_u32(r - __uint_as_float(mid << 16));
+}
+
 // Compute units of the current device (cached per device).
 int device_cus();
 
@@ -166,6 +185,12 @@ hipError_t launch_narrow_fwd(const GemmArgs &g, hipStream_t s);
 bool gemm_async_applies(const GemmArgs &g);
 size_t gemm_async_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm_async(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
+
+// ---- contractions whose operand parts are staged together (gemm_joint.hip) -----
+bool gemm_joint_applies(const GemmArgs &g);
+double gemm_joint_us(const GemmArgs &g);  // estimated time, 1e300 if not applicable
+size_t gemm_joint_workspace_bytes(const GemmArgs &g);
+hipError_t launch_gemm_joint(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
 
 // dst[c*ld_dst + k] = src[row(k)*ld_src + c] for k < rows, c < cols, with
 // row(k) = k, or, when perm_T > 0, row(k) = (k % perm_T) * (rows / perm_T) +

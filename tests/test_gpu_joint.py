@@ -1,0 +1,117 @@
+"""Contractions of odd sizes through the stage calls, at the edges of the tiles,
+k-tiles and splits of the kernels that stage all parts of an operand together.
+
+Each product is compared with the fp64 product of the same values.  Bound: an
+fp32 sum of K exact products in any order is within (K + 2) 2^-24 of the sum
+of its terms' magnitudes; the fp32 x fp32 input gradient takes six of the nine
+part products (6 K terms, and 2^-26 of each term left out).
+"""
+import numpy as np
+import pytest
+
+import paper_2211_10725_amd as snn
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# rows, n_in, n_out: tiles with one row or column past a multiple of 128 / 256,
+# k-tiles with 1 .. 63 valid values, widths that are not whole 16-byte chunks
+SHAPES = [(2049, 769, 705), (4097, 521, 513), (1281, 1003, 1101), (16390, 257, 264),
+          (1025, 4104, 256), (8193, 200, 776), (300, 2048, 2056)]
+
+
+def _layer(M, n_in, n_out, half, seed, grad_dtype=None):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    x = (torch.rand((M, n_in), generator=g, device="cuda") < 0.4)
+    W = torch.rand((n_out, n_in), generator=g, device="cuda") * 2 - 1
+    b = torch.rand(n_out, generator=g, device="cuda") * 2 - 1
+    dI = torch.randn((M, n_out), generator=g, device="cuda")
+    spec = dict(kind="dense", n_in=n_in, n_out=n_out, neuron="leaky", beta=0.9)
+    if half:
+        x, W, dI = x.half(), W.half(), dI.half()
+        d = snn.layer_desc(spec, 1, M, in_dtype=snn.F16, w_dtype=snn.F16, grad_dtype=snn.F16)
+    else:
+        x = x.to(torch.uint8)
+        d = snn.layer_desc(spec, 1, M)
+    return d, x, W, b, dI
+
+
+def _within(got, ref, terms, n, extra, what):
+    err = (got.double() - ref).abs()
+    bound = ((n + 2) * 2.0 ** -24 + extra) * terms
+    assert bool((err <= bound).all()), f"{what}: {float((err / bound.clamp_min(1e-300)).max()):.2f}"
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("M,n_in,n_out", SHAPES)
+def test_ragged_contractions(M, n_in, n_out, half):
+    d, x, W, b, dI = _layer(M, n_in, n_out, half, M + n_in)
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    cur = torch.full((M, n_out), float("nan"), device="cuda")
+    gW = torch.full((n_out, n_in), float("nan"), device="cuda")
+    gx = torch.full((M, n_in), float("nan"), device="cuda")
+    S = 8.0 if half else 1.0
+    scale = torch.full((4,), S, device="cuda")
+    snn.snn_synapse_fwd(d, x, W, b, cur, None, ws)
+    snn.snn_synapse_bwd(d, dI, None, x, W, gW, gx, ws, dcur_scale=scale if half else None)
+    xd, Wd, bd, dd = x.double(), W.double(), b.double(), dI.double() / S
+    _within(cur, xd @ Wd.t() + bd, xd @ Wd.abs().t() + bd.abs(), n_in + 1, 0.0, "currents")
+    _within(gW, dd.t() @ xd, dd.abs().t() @ xd, M, 0.0, "dW")
+    _within(gx, dd @ Wd, dd.abs() @ Wd.abs(), n_out if half else 6 * n_out,
+            0.0 if half else 2.0 ** -26, "dx")
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(2049, 769, 705), (3000, 640, 768)])
+def test_bf16_spikes_match_bytes(M, n_in, n_out):
+    """Spikes given as bf16 0/1 are contracted in the same order as bytes."""
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, 5)
+    out = []
+    for t in (snn.U8, snn.BF16):
+        e = d.copy()
+        e.in_dtype = t
+        xi = x if t == snn.U8 else x.bfloat16()
+        ws = torch.empty(snn.snn_layer_workspace_bytes(e) + 256, dtype=torch.uint8, device="cuda")
+        cur = torch.empty((M, n_out), device="cuda")
+        gW = torch.empty((n_out, n_in), device="cuda")
+        snn.snn_synapse_fwd(e, xi, W, b, cur, None, ws)
+        snn.snn_synapse_bwd(e, dI, None, xi, W, gW, None, ws)
+        out.append((cur, gW))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("from_planes", [False, True])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+def test_input_gradient_of_special_values(bad, from_planes):
+    """An infinity, NaN or value near fp32's largest in dL/dI or W gives the
+    input gradient the fp32 products give, not the NaN of its parts; its last
+    value sits in a partial k-tile.  Both with dL/dI in fp32 and as the planes
+    the reverse scan writes (the layer call)."""
+    M, n_in, n_out = 1600, 768, 1000
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, 9)
+    W[999, 3] = bad
+    W[:, 700] = 0.0
+    if not from_planes:
+        dI[5, 999] = bad
+        dI[77, 40] = bad
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    gx = torch.empty((M, n_in), device="cuda")
+    if from_planes:
+        cur = torch.zeros((M, n_out), device="cuda")
+        assert snn.snn_layer_dcur_t_layout(d) == snn.DCUR_T_PLANES
+        dI[5, 999] = bad
+        saved = torch.zeros(snn.snn_layer_saved_bytes(d), dtype=torch.uint8, device="cuda")
+        snn.saved_parts(d, saved)[0].copy_(cur.view(1, M, n_out))
+        gW = torch.empty_like(W)
+        snn.snn_layer_bwd(d, snn.GRAD_FULL, dI, x, W, None, saved, gW, None, None, gx, ws)
+        sg = torch.tensor(1.0, device="cuda") / (1.0 + torch.tensor(25.0, device="cuda")) ** 2
+        dI = dI * sg
+    else:
+        snn.snn_synapse_bwd(d, dI, None, x, W, None, gx, ws)
+    ref = (dI.double() @ W.double()).float()  # overflows to infinity as the fp32 sum does
+    fin = torch.isfinite(ref)
+    assert torch.equal(torch.isnan(gx), torch.isnan(ref))
+    assert torch.equal(torch.isinf(gx), torch.isinf(ref))
+    assert torch.equal(gx[torch.isinf(ref)], ref[torch.isinf(ref)])
+    tol = (6 * n_out + 6) * 2.0 ** -24 * (dI[:, :].double().abs() @ W.double().abs())
+    assert bool(((gx.double() - ref.double()).abs()[fin] <= tol[fin]).all())
