@@ -18,38 +18,10 @@
 // running the chunk backwards.
 #include <atomic>
 
-#include "neuron.hpp"
+#include "scan_common.hpp"
 
 namespace snn {
 namespace {
-
-constexpr int kThreads = 256;
-// Lanes own 2 columns when there are enough columns to fill the chip (2^19:
-// 4096 waves of 2-column lanes; on the 65536 x 64-column layer 2 columns and
-// 16 steps ahead measured 4-7 % faster than 4 columns and 8 steps, and 1
-// column slower still), otherwise 1; the forward loads 16 steps ahead.
-constexpr int kWideColumns = 4 * 64 * 2048;
-constexpr int kCkpt = kCheckpointInterval;  // steps per recomputed chunk
-constexpr int kFoldMax = 16;   // most outputs of a dense layer whose input gradient is folded
-constexpr int kFoldRows = 5;   // batch rows one workgroup's columns can span when folding
-
-template <int VEC>
-struct Vec;
-template <>
-struct Vec<2> {
-    static __device__ inline void load(const float *p, float (&v)[2]) {
-        const float2 x = *reinterpret_cast<const float2 *>(p);
-        v[0] = x.x; v[1] = x.y;
-    }
-    static __device__ inline void store(float *p, const float (&v)[2]) {
-        *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
-    }
-};
-template <>
-struct Vec<1> {
-    static __device__ inline void load(const float *p, float (&v)[1]) { v[0] = *p; }
-    static __device__ inline void store(float *p, const float (&v)[1]) { *p = v[0]; }
-};
 
 // spikes as bytes 0/1
 template <int VEC>
@@ -92,14 +64,22 @@ __device__ inline void store_spikes_bits(uint64_t *words, int64_t wave_off, cons
 }
 
 // Forward scan.  Writes the spikes, the spike counts (nullable), the full
-// membrane (u_out, nullable; it may alias cur exactly: each lane reads step
-// t before it writes it) and the checkpoints: after step t with
+// membrane (u_out with UOUT; it may alias cur exactly: each lane reads step t
+// before it writes it) and the checkpoints: after step t with
 // (t + 1) % kCkpt == 0 and t + 1 < T, u to ckpt[(t + 1) / kCkpt - 1][C]
 // and, for the current-based neuron, i to the same slot of a second plane
 // nck chunks further.  The recurrent neuron (eq. 7) adds its own previous
 // spike through the recurrent weight: a spike at t-1 adds (v - thr) to u_t
 // instead of the plain reset -thr; column c is neuron c % N.
-template <int NEURON, int VEC, int OUT, int kDepth>
+//
+// Blocks of kCkpt steps run from NB register sets in turn, the loads of the
+// block NB - 1 further issued before a block's steps.  A whole block has no
+// branches (loads past T repeat the last row): vector memory operations
+// complete in order and the compiler counts them, so a branch around a store
+// makes it wait for every load and store in flight, once per block.  That wait
+// bounded layers of few waves, which leave nothing to run meanwhile (1000 steps
+// of 65536 columns: 113 -> 76 us).
+template <int NEURON, int VEC, int OUT, int NB, bool UOUT>
 __global__ __launch_bounds__(kThreads) void neuron_fwd_kernel(int T, int64_t C, int64_t N,
                                                               float alpha, float beta, float thr,
                                                               const float *__restrict__ vrec,
@@ -107,7 +87,7 @@ __global__ __launch_bounds__(kThreads) void neuron_fwd_kernel(int T, int64_t C, 
                                                               float *u_out,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ counts) {
-    static_assert(kCkpt % kDepth == 0, "checkpoints fall on block boundaries");
+    constexpr int D = kCkpt;
     // packed-bit output with two columns per lane: the lane's columns are col
     // and col + 64 (see store_spikes_bits), else col and col + 1
     constexpr bool SPLIT = OUT == SNN_SPK_BITS && VEC == 2;
@@ -140,410 +120,54 @@ __global__ __launch_bounds__(kThreads) void neuron_fwd_kernel(int T, int64_t C, 
         else jump[v] = -thr;
     }
 
-    float in[kDepth][VEC], nx[kDepth][VEC];
+    float in[NB][D][VEC];
+    auto load = [&](int t0, float (&x)[D][VEC]) {
 #pragma unroll
-    for (int j = 0; j < kDepth; ++j)
-        if (j < T) ld(cur + (int64_t)j * C + col, in[j]);
-
-    for (int t0 = 0; t0 < T; t0 += kDepth) {
-#pragma unroll
-        for (int j = 0; j < kDepth; ++j)
-            if (t0 + kDepth + j < T) ld(cur + (int64_t)(t0 + kDepth + j) * C + col, nx[j]);
-#pragma unroll
-        for (int j = 0; j < kDepth; ++j) {
-            const int t = t0 + j;
-            if (t < T) {
-                float z[VEC];
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float uu = neuron_step<NEURON>(u[v], syn[v], zp[v], in[j][v], alpha,
-                                                         beta, jump[v]);
-                    z[v] = (uu > thr) ? 1.f : 0.f;       // eq. (3), strict
-                    zp[v] = z[v];
-                    cnt[v] += z[v];
-                }
-                const int64_t off = (int64_t)t * C + col;
-                if (u_out) st(u_out + off, u);
-                if constexpr (OUT == SNN_U8)
-                    store_spikes_u8<VEC>(reinterpret_cast<uint8_t *>(spk) + off, z);
-                else if constexpr (OUT == SNN_SPK_BITS)
-                    store_spikes_bits<VEC>(reinterpret_cast<uint64_t *>(spk),
-                                           off - (threadIdx.x & 63), z);
-                else
-                    store_spikes_f16<VEC>(reinterpret_cast<uint16_t *>(spk) + off, z);
-            }
-        }
-        const int tn = t0 + kDepth;  // steps done
-        if (tn % kCkpt == 0 && tn < T) {
-            const int64_t slot = (int64_t)(tn / kCkpt - 1) * C + col;
-            st(ckpt + slot, u);
-            if constexpr (NEURON == SNN_SYNAPTIC) st(ckpt + (int64_t)nck * C + slot, syn);
-        }
-#pragma unroll
-        for (int j = 0; j < kDepth; ++j)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) in[j][v] = nx[j][v];
-    }
-    if (counts) st(counts + col, cnt);
-}
-
-__device__ inline uint16_t f32_to_bf16_rne(float x) {
-    const uint32_t b = __float_as_uint(x);
-    return (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
-}
-
-// dL/dI in the operand type of the contractions.  fp16 is written scaled by
-// the power of two `scale` (exact), chosen per call so that every value
-// stays below 2^15 (grad_scale_*_kernel below).
-template <int GT, int VEC>
-__device__ inline void store_grad(void *base, int64_t off, const float (&v)[VEC], float scale) {
-    if constexpr (GT == SNN_F32) {
-        Vec<VEC>::store(reinterpret_cast<float *>(base) + off, v);
-    } else {
-        uint16_t h[VEC];
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            if constexpr (GT == SNN_F16) {
-                const _Float16 f = (_Float16)(v[i] * scale);
-                h[i] = __builtin_bit_cast(uint16_t, f);
-            } else {
-                h[i] = f32_to_bf16_rne(v[i]);
-            }
-        }
-        uint16_t *p = reinterpret_cast<uint16_t *>(base) + off;
-        if constexpr (VEC == 2)
-            *reinterpret_cast<uint32_t *>(p) = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-        else
-            p[0] = h[0];
-    }
-}
-
-// The 16-bit parts of dL/dI for the weight-gradient contraction: fp32 as
-// three exact bf16 parts (hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi
-// - mid), each subtraction exact), bf16 or fp16 (scaled) as one.
-__device__ inline uint32_t bf16_rne_bits(float x) { return f32_to_bf16_rne(x); }
-template <int GT>
-__device__ inline uint32_t grad_part(float x, int p, float scale) {
-    if constexpr (GT == SNN_F16) {
-        const _Float16 f = (_Float16)(x * scale);
-        return __builtin_bit_cast(uint16_t, f);
-    } else if constexpr (GT == SNN_BF16) {
-        return bf16_rne_bits(x);
-    } else {
-        const uint32_t hi = bf16_rne_bits(x);
-        if (p == 0) return hi;
-        const float r = x - __uint_as_float(hi << 16);
-        const uint32_t mid = bf16_rne_bits(r);
-        if (p == 1) return mid;
-        return bf16_rne_bits(r - __uint_as_float(mid << 16));
-    }
-}
-
-// Sources of the upstream gradient g_t = dL/dz_t of the reverse scan.
-constexpr int GM_FULL = 0;   // g [T, C]
-constexpr int GM_BCAST = 1;  // g [C], the same for every t
-constexpr int GM_FOLD = 2;   // g_t[b, n] = sum_j dI_up[t, b, j] W_up[j, n]: the input
-                             // gradient of a dense layer above with at most
-                             // kFoldMax outputs, computed here instead of read
-constexpr int GM_FOLD12 = 3; // the same for at most 12 outputs (10 classes)
-
-// The layer above, for GM_FOLD.  A workgroup's 256 VEC consecutive columns
-// span at most kFoldRows batch rows (the launcher only folds layers with
-// n >= 64, and n >= 128 for VEC = 2); the dI_up rows of those batch rows for
-// one chunk of kCkpt steps are staged in LDS (double-buffered, one barrier
-// per chunk), the next chunk's loaded into registers while this one runs.
-struct FoldIn {
-    const void *dup;  // [T, B, nup] of dt_up
-    const void *wup;  // [nup, N] of dt_w
-    int nup, dt_up, dt_w, B;
-};
-
-__device__ inline float load_as_f32(const void *p, int64_t i, int dt) {
-    if (dt == SNN_F32) return reinterpret_cast<const float *>(p)[i];
-    const uint16_t h = reinterpret_cast<const uint16_t *>(p)[i];
-    if (dt == SNN_BF16) return __uint_as_float((uint32_t)h << 16);
-    return (float)__builtin_bit_cast(_Float16, h);
-}
-
-template <int KF>
-struct FoldStage {
-    static constexpr int kElems = kCkpt * kFoldRows * KF;
-    static constexpr int kPer = (kElems + 255) / 256;  // per thread (256-thread blocks)
-    float v[kPer];
-
-    // the dI_up values of the steps t0 .. t0 + kCkpt - 1 of a chunk and batch
-    // rows b_lo .. b_lo + kFoldRows - 1 (zeros outside)
-    __device__ inline void load(const FoldIn &f, int T, int t0, int64_t b_lo) {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int e = threadIdx.x + i * 256;
-            const int jt = e / (kFoldRows * KF), bb = (e / KF) % kFoldRows, j = e % KF;
-            const int t = t0 + jt;
-            const int64_t b = b_lo + bb;
-            v[i] = (e < kElems && t < T && b < f.B && j < f.nup)
-                       ? load_as_f32(f.dup, ((int64_t)t * f.B + b) * f.nup + j, f.dt_up)
-                       : 0.f;
-        }
-    }
-    __device__ inline void store(float *rows) const {
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int e = threadIdx.x + i * 256;
-            if (e < kElems) rows[e] = v[i];
-        }
-    }
-};
-
-// Reverse-time scan over chunks of kCkpt steps, last chunk first.  For each
-// chunk the lane loads its currents and the checkpoint before it (prefetched
-// while the previous chunk runs), recomputes u_t forward in registers, then
-// runs the adjoint backwards.  lam carries dL/du_{t+1} (and lami dL/di_{t+1}).
-// For the recurrent neuron the spike z_t reaches u_{t+1} through
-// (v - r thr), so the carry is beta + (v - r thr) s_t, and the recurrent
-// weight's gradient collects lam_{t+1} z_t per column (dvcol, fp32).
-//
-// With TR = TR_TRANSPOSED, dL/dI is also written as the weight gradient's
-// operand: dcur_t [P][N][B*T] (P = 3 bf16 parts of fp32, else 1 plane of the
-// 16-bit type, planes t_plane elements apart), row n holding column n of
-// every sample, K index b*T + t.  A lane's column is one row there and a
-// chunk's steps are consecutive in it, so each chunk's values are packed in
-// registers as the reverse loop produces them and stored together.  With
-// TR = TR_PLANES (fp32 only), dcur_t holds the three bf16 parts in dcur's own
-// layout, [3][T][C], written at every step like dcur.  The row-major dcur
-// may be skipped (nullptr) in both cases.
-constexpr int TR_NONE = 0, TR_TRANSPOSED = 1, TR_PLANES = 2;
-template <int NEURON, int VEC, int GM, bool RESET_SURR, int GT, int TRM>
-__global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
-    int T, int64_t C, int64_t N, float alpha, float beta, float thr, float slope,
-    const float *__restrict__ vrec, const float *__restrict__ cur, const float *__restrict__ ckpt,
-    const float *__restrict__ g, FoldIn fold, void *__restrict__ dcur,
-    uint16_t *__restrict__ dcur_t, int64_t t_plane,
-    const float *__restrict__ dscale, float *__restrict__ colsum, float *__restrict__ dvcol) {
-    constexpr bool BCAST = GM == GM_BCAST, FOLD = GM == GM_FOLD || GM == GM_FOLD12;
-    constexpr bool FULL = GM == GM_FULL;
-    constexpr int K = kCkpt;
-    constexpr int P = GT == SNN_F32 ? 3 : 1;  // 16-bit parts per value in dcur_t
-    constexpr bool TR = TRM == TR_TRANSPOSED;
-    uint32_t pk[TR ? P : 1][TR ? VEC : 1][TR ? K / 2 : 1];  // packed parts of a chunk
-    const float scale = GT == SNN_F16 ? *dscale : 1.f;
-    constexpr int KF = GM == GM_FOLD12 ? 12 : kFoldMax;  // dI_up values per row (padded)
-    const int64_t col = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
-    // the fold's lanes past the last column still take part in the staging
-    const bool active = col < C;
-    if (!FOLD && !active) return;
-    const int nch = (T + K - 1) / K, nck = nch - 1;
-    float lam[VEC], lami[VEC], acc[VEC], gb[VEC], vr[VEC], dv[VEC], jump[VEC];
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-        lam[v] = lami[v] = acc[v] = gb[v] = dv[v] = 0.f;
-        const float vv = (NEURON == SNN_RLEAKY && active) ? vrec[(col + v) % N] : 0.f;
-        jump[v] = NEURON == SNN_RLEAKY ? vv - thr : -thr;
-        vr[v] = NEURON == SNN_RLEAKY ? (RESET_SURR ? vv - thr : vv) : 0.f;
-    }
-    if constexpr (BCAST) Vec<VEC>::load(g + col, gb);
-
-    // fold: the lane's columns of W_up, its batch row within the staged rows
-    __shared__ __attribute__((aligned(16))) float frows[FOLD ? 2 : 1][FOLD ? FoldStage<KF>::kElems : 1];
-    float wcol[FOLD ? VEC : 1][FOLD ? KF : 1];
-    int fbb = 0;
-    int64_t b_lo = 0;
-    FoldStage<KF> fst;
-    if constexpr (FOLD) {
-        b_lo = ((int64_t)blockIdx.x * kThreads * VEC) / N;
-        fbb = active ? (int)(col / N - b_lo) : 0;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v)
-#pragma unroll
-            for (int j = 0; j < KF; ++j)
-                wcol[v][j] = (active && j < fold.nup)
-                                 ? load_as_f32(fold.wup, (int64_t)j * N + (col + v) % N, fold.dt_w)
-                                 : 0.f;
-        fst.load(fold, T, nck * K, b_lo);
-        fst.store(frows[nck & 1]);
-        if (nck >= 1) fst.load(fold, T, (nck - 1) * K, b_lo);
-        __syncthreads();
-    }
-
-    // chunk registers: currents (then the recomputed membrane) of this chunk
-    // and of the one before it, the full upstream gradient likewise, and the
-    // checkpointed state at the start of each
-    float ii[K][VEC], ni[K][VEC];
-    float gg[FULL ? K : 1][VEC], ng[FULL ? K : 1][VEC];
-    float cu[VEC], ci[VEC], nu[VEC], nci[VEC];
-    auto load_chunk = [&](int c, float (&xi)[K][VEC], float (&xg)[FULL ? K : 1][VEC],
-                          float (&su)[VEC], float (&si)[VEC]) {
-        const int t_lo = c * K;
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            if (t_lo + j < T) {
-                Vec<VEC>::load(cur + (int64_t)(t_lo + j) * C + col, xi[j]);
-                if constexpr (FULL) Vec<VEC>::load(g + (int64_t)(t_lo + j) * C + col, xg[j]);
-            }
-        }
-        if (c > 0) {
-            Vec<VEC>::load(ckpt + (int64_t)(c - 1) * C + col, su);
-            if constexpr (NEURON == SNN_SYNAPTIC)
-                Vec<VEC>::load(ckpt + (int64_t)(nck + c - 1) * C + col, si);
-            else
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) si[v] = 0.f;
-        } else {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) su[v] = si[v] = 0.f;
-        }
+        for (int j = 0; j < D; ++j) ld(cur + (int64_t)min(t0 + j, T - 1) * C + col, x[j]);
     };
-    if (active) load_chunk(nck, ii, gg, cu, ci);
-
-    for (int c = nck; c >= 0; --c) {
-        const int t_lo = c * K;
-        if (active) {
-            if (c > 0) load_chunk(c - 1, ni, ng, nu, nci);
-            // recompute u_t of the chunk from the state before it (u_{t_lo-1},
-            // i_{t_lo-1}; z_{t_lo-1} = [u_{t_lo-1} > thr]), in place of I_t
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                float u = cu[v], syn = ci[v];
-                float zp = (c > 0 && cu[v] > thr) ? 1.f : 0.f;
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    if (t_lo + j < T) {
-                        const float uu = neuron_step<NEURON>(u, syn, zp, ii[j][v], alpha, beta,
-                                                             jump[v]);
-                        ii[j][v] = uu;
-                        zp = (uu > thr) ? 1.f : 0.f;
-                    }
-                }
-            }
-        }
-        const float *fr = FOLD ? frows[c & 1] : nullptr;
-        if constexpr (TR) {
-#pragma unroll
-            for (int p = 0; p < P; ++p)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v)
-#pragma unroll
-                    for (int q = 0; q < K / 2; ++q) pk[p][v][q] = 0u;
-        }
-#pragma unroll
-        for (int j = K - 1; j >= 0; --j) {
-            const int t = t_lo + j;
-            if (t < T && active) {
-                float d[VEC];
-                float grow[FOLD ? KF : 1];
-                if constexpr (FOLD) {
-                    const float4 *r4 = reinterpret_cast<const float4 *>(
-                        fr + (j * kFoldRows + fbb) * KF);
-#pragma unroll
-                    for (int q = 0; q < KF / 4; ++q) {
-                        const float4 x = r4[q];
-                        grow[4 * q] = x.x; grow[4 * q + 1] = x.y;
-                        grow[4 * q + 2] = x.z; grow[4 * q + 3] = x.w;
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float uu = ii[j][v];
-                    const float s = surrogate(uu, thr, slope);
-                    float gt;
-                    if constexpr (BCAST) {
-                        gt = gb[v];
-                    } else if constexpr (FOLD) {
-                        gt = 0.f;  // j ascending: the order of the short contraction
-#pragma unroll
-                        for (int q = 0; q < KF; ++q) gt = __builtin_fmaf(grow[q], wcol[v][q], gt);
-                    } else {
-                        gt = gg[j][v];
-                    }
-                    if constexpr (NEURON == SNN_RLEAKY) {
-                        if (uu > thr) dv[v] += lam[v];  // lam_{t+1} z_t
-                        const float carry = __builtin_fmaf(vr[v], s, beta);
-                        lam[v] = __builtin_fmaf(carry, lam[v], gt * s);
-                        d[v] = lam[v];
-                    } else {
-                        d[v] = adjoint_step<NEURON, RESET_SURR>(lam[v], lami[v], gt, s, alpha,
-                                                                beta, thr);
-                    }
-                    acc[v] += d[v];
-                }
-                if (dcur) store_grad<GT, VEC>(dcur, (int64_t)t * C + col, d, scale);
-                if constexpr (TRM == TR_PLANES) {
-                    uint32_t part[3][VEC];
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v)
-                        split_bf16x3(d[v], part[0][v], part[1][v], part[2][v]);
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) {
-                        uint16_t *q = dcur_t + p * t_plane + (int64_t)t * C + col;
-                        if constexpr (VEC == 2)
-                            *reinterpret_cast<uint32_t *>(q) = part[p][0] | (part[p][1] << 16);
-                        else
-                            q[0] = (uint16_t)part[p][0];
-                    }
-                }
-                if constexpr (TR) {
-#pragma unroll
-                    for (int p = 0; p < P; ++p)
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) {
-                            const uint32_t h = grad_part<GT>(d[v], p, scale);
-                            pk[p][v][j / 2] |= (j & 1) ? h << 16 : h;
-                        }
-                }
-            }
-        }
-        if constexpr (TR) {
-            // the chunk's steps of this lane's columns, row (col + v) % N,
-            // K index b*T + t
-            if (active) {
-                const int len = min(K, T - t_lo);
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const int64_t n = (col + v) % N, b = (col + v) / N;
-                    const int64_t base = n * ((int64_t)T * (C / N)) + b * T + t_lo;
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        uint16_t *row = dcur_t + p * t_plane + base;
-                        if (len == K && (T & 3) == 0) {
-#pragma unroll
-                            for (int q = 0; q < K / 4; ++q)
-                                *reinterpret_cast<uint2 *>(row + 4 * q) =
-                                    make_uint2(pk[p][v][2 * q], pk[p][v][2 * q + 1]);
-                        } else {
-#pragma unroll
-                            for (int jj = 0; jj < K; ++jj)
-                                if (jj < len)
-                                    row[jj] = (uint16_t)(pk[p][v][jj / 2] >> (16 * (jj & 1)));
-                        }
-                    }
-                }
-            }
-        }
-        if constexpr (FOLD) {
-            // stage the next chunk (its buffer was last read before the
-            // previous barrier), then load the one after it
-            if (c >= 1) {
-                fst.store(frows[(c - 1) & 1]);
-                if (c >= 2) fst.load(fold, T, (c - 2) * K, b_lo);
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                ii[j][v] = ni[j][v];
-                if constexpr (FULL) gg[j][v] = ng[j][v];
-            }
+    auto step = [&](int t, const float (&x)[VEC]) {
+        float z[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            cu[v] = nu[v];
-            ci[v] = nci[v];
+            const float uu = neuron_step<NEURON>(u[v], syn[v], zp[v], x[v], alpha, beta, jump[v]);
+            z[v] = (uu > thr) ? 1.f : 0.f;  // eq. (3), strict
+            zp[v] = z[v];
+            cnt[v] += z[v];
+        }
+        const int64_t off = (int64_t)t * C + col;
+        if constexpr (UOUT) st(u_out + off, u);
+        if constexpr (OUT == SNN_U8)
+            store_spikes_u8<VEC>(reinterpret_cast<uint8_t *>(spk) + off, z);
+        else if constexpr (OUT == SNN_SPK_BITS)
+            store_spikes_bits<VEC>(reinterpret_cast<uint64_t *>(spk), off - (threadIdx.x & 63), z);
+        else
+            store_spikes_f16<VEC>(reinterpret_cast<uint16_t *>(spk) + off, z);
+    };
+#pragma unroll
+    for (int b = 0; b < (NB > 1 ? NB - 1 : 1); ++b) load(b * D, in[b]);
+    for (int t0 = 0; t0 < T; t0 += NB * D) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int tb = t0 + b * D;
+            if (tb + D <= T) {
+                if constexpr (NB > 1) load(tb + (NB - 1) * D, in[(b + NB - 1) % NB]);
+#pragma unroll
+                for (int j = 0; j < D; ++j) step(tb + j, in[b][j]);
+                if (tb + D < T) {
+                    const int64_t slot = (int64_t)(tb / kCkpt) * C + col;
+                    st(ckpt + slot, u);
+                    if constexpr (NEURON == SNN_SYNAPTIC) st(ckpt + (int64_t)nck * C + slot, syn);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < D; ++j)
+                    if (tb + j < T) step(tb + j, in[b][j]);
+                t0 = T;
+                break;
+            }
         }
     }
-    if (!active) return;
-    if (colsum) Vec<VEC>::store(colsum + col, acc);
-    if constexpr (NEURON == SNN_RLEAKY)
-        if (dvcol) Vec<VEC>::store(dvcol + col, dv);
+    if (counts) st(counts + col, cnt);
 }
 
 // Bias gradient: db[f] = sum over b of the per-column time sums.  A block
@@ -624,8 +248,30 @@ __global__ __launch_bounds__(kThreads) void grad_bound_kernel(int64_t rows, int 
                                                               const void *__restrict__ w,
                                                               float *__restrict__ partial) {
     __shared__ float red[kThreads / 64];
-    // rows of `width` values: the max over rows of sum |x| (width 1: max |x|)
+    // rows of `width` values: the max over rows of sum |x| (width 1: max |x|,
+    // an fp32 gradient of every step read 64 bytes per lane at a time: 26 MB
+    // in 11.7 us one value at a time)
     float m1 = 0.f;
+    if (width == 1) {
+        const float4 *x4 = reinterpret_cast<const float4 *>(src);
+        const int64_t n4 = rows / 4, step = (int64_t)gridDim.x * kThreads;
+        int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+        auto take = [&](const float4 &v) {
+            m1 = fmaxf(fmaxf(m1, fmaxf(__builtin_fabsf(v.x), __builtin_fabsf(v.y))),
+                       fmaxf(__builtin_fabsf(v.z), __builtin_fabsf(v.w)));
+        };
+        for (; i + 3 * step < n4; i += 4 * step) {
+            float4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = x4[i + q * step];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) take(v[q]);
+        }
+        for (; i < n4; i += step) take(x4[i]);
+        if (blockIdx.x == 0 && threadIdx.x < rows - 4 * n4)
+            m1 = fmaxf(m1, __builtin_fabsf(reinterpret_cast<const float *>(src)[4 * n4 + threadIdx.x]));
+        rows = 0;
+    }
     for (int64_t r = (int64_t)blockIdx.x * kThreads + threadIdx.x; r < rows;
          r += (int64_t)gridDim.x * kThreads) {
         float a = 0.f;
@@ -675,25 +321,28 @@ __global__ __launch_bounds__(kThreads) void fill_zero_kernel(float *__restrict__
     if (i < n) p[i] = 0.f;
 }
 
-struct ScanArgs {
-    int T;
-    int64_t C, N;
-    float alpha, beta, thr, slope;
-    const float *vrec;
-};
-
 struct FwdBuffers {
     const float *cur;
     void *spk;
     float *u_out, *ckpt, *counts;
 };
 
-template <int NEURON, int VEC, int OUT>
-void fwd_launch(const ScanArgs &a, const FwdBuffers &b, hipStream_t s) {
+template <int NEURON, int VEC, int OUT, int NB, bool UOUT>
+void fwd_launch_nb(const ScanArgs &a, const FwdBuffers &b, hipStream_t s) {
     const int64_t lanes = (a.C + VEC - 1) / VEC;
     const unsigned grid = (unsigned)((lanes + kThreads - 1) / kThreads);
-    neuron_fwd_kernel<NEURON, VEC, OUT, 16><<<grid, kThreads, 0, s>>>(
+    neuron_fwd_kernel<NEURON, VEC, OUT, NB, UOUT><<<grid, kThreads, 0, s>>>(
         a.T, a.C, a.N, a.alpha, a.beta, a.thr, a.vrec, b.cur, b.spk, b.u_out, b.ckpt, b.counts);
+}
+
+// Blocks in registers: one for sequences of one block, else two (four measured
+// slower: 27.0 against 23.3 us on 100 steps of 262144 columns, 16.6 against 14.3
+// on 50 current-based steps of 256000).
+template <int NEURON, int VEC, int OUT>
+void fwd_launch(const ScanArgs &a, const FwdBuffers &b, hipStream_t s) {
+    if (b.u_out) fwd_launch_nb<NEURON, VEC, OUT, 2, true>(a, b, s);
+    else if (a.T <= kCkpt) fwd_launch_nb<NEURON, VEC, OUT, 1, false>(a, b, s);
+    else fwd_launch_nb<NEURON, VEC, OUT, 2, false>(a, b, s);
 }
 
 template <int NEURON, int VEC>
@@ -701,71 +350,6 @@ void fwd_dispatch(int out_dtype, const ScanArgs &a, const FwdBuffers &b, hipStre
     if (out_dtype == SNN_U8) fwd_launch<NEURON, VEC, SNN_U8>(a, b, s);
     else if (out_dtype == SNN_SPK_BITS) fwd_launch<NEURON, VEC, SNN_SPK_BITS>(a, b, s);
     else fwd_launch<NEURON, VEC, SNN_F16>(a, b, s);
-}
-
-struct BwdBuffers {
-    const float *cur, *ckpt, *g;
-    FoldIn fold;
-    void *dcur;
-    uint16_t *dcur_t;
-    bool planes;  // dcur_t holds the planes of an fp32 dL/dI in dcur's layout
-    const float *dscale;
-    float *colsum, *dvcol;
-};
-
-template <int NEURON, int VEC, int GM, bool RS, int GT>
-void bwd_launch(const ScanArgs &a, const BwdBuffers &b, hipStream_t s) {
-    const int64_t lanes = (a.C + VEC - 1) / VEC;
-    const unsigned grid = (unsigned)((lanes + kThreads - 1) / kThreads);
-    const int64_t t_plane = (int64_t)a.T * a.C;
-    if (b.dcur_t && b.planes) {
-        if constexpr (GT == SNN_F32)
-            neuron_bwd_kernel<NEURON, VEC, GM, RS, GT, TR_PLANES><<<grid, kThreads, 0, s>>>(
-                a.T, a.C, a.N, a.alpha, a.beta, a.thr, a.slope, a.vrec, b.cur, b.ckpt, b.g,
-                b.fold, b.dcur, b.dcur_t, t_plane, b.dscale, b.colsum, b.dvcol);
-    } else if (b.dcur_t) {
-        neuron_bwd_kernel<NEURON, VEC, GM, RS, GT, TR_TRANSPOSED><<<grid, kThreads, 0, s>>>(
-            a.T, a.C, a.N, a.alpha, a.beta, a.thr, a.slope, a.vrec, b.cur, b.ckpt, b.g, b.fold,
-            b.dcur, b.dcur_t, t_plane, b.dscale, b.colsum, b.dvcol);
-    } else {
-        neuron_bwd_kernel<NEURON, VEC, GM, RS, GT, TR_NONE><<<grid, kThreads, 0, s>>>(
-            a.T, a.C, a.N, a.alpha, a.beta, a.thr, a.slope, a.vrec, b.cur, b.ckpt, b.g, b.fold,
-            b.dcur, nullptr, 0, b.dscale, b.colsum, b.dvcol);
-    }
-}
-
-template <int NEURON, int VEC, int GM, bool RS>
-void bwd_dispatch_gt(int gt, const ScanArgs &a, const BwdBuffers &b, hipStream_t s) {
-    if (gt == SNN_F32) bwd_launch<NEURON, VEC, GM, RS, SNN_F32>(a, b, s);
-    else if (gt == SNN_F16) bwd_launch<NEURON, VEC, GM, RS, SNN_F16>(a, b, s);
-    else bwd_launch<NEURON, VEC, GM, RS, SNN_BF16>(a, b, s);
-}
-
-template <int NEURON, int VEC, int GM>
-void bwd_dispatch_rs(int rs, int gt, const ScanArgs &a, const BwdBuffers &b, hipStream_t s) {
-    if (rs) bwd_dispatch_gt<NEURON, VEC, GM, true>(gt, a, b, s);
-    else bwd_dispatch_gt<NEURON, VEC, GM, false>(gt, a, b, s);
-}
-
-// Lane widths: two columns for layers of at least kWideColumns columns
-// (measured on the 65536 x 64-column layer: 7.0 against 7.4 ms for four
-// columns per lane, whose chunk registers left two waves per SIMD), else one.
-template <int NEURON>
-void bwd_dispatch(int vec, int rs, int gm, int gt, const ScanArgs &a, const BwdBuffers &b,
-                  hipStream_t s) {
-    if (gm == GM_BCAST) {
-        if (vec == 2) bwd_dispatch_rs<NEURON, 2, GM_BCAST>(rs, gt, a, b, s);
-        else bwd_dispatch_rs<NEURON, 1, GM_BCAST>(rs, gt, a, b, s);
-    } else if (gm == GM_FOLD12) {
-        if (vec == 2) bwd_dispatch_rs<NEURON, 2, GM_FOLD12>(rs, gt, a, b, s);
-        else bwd_dispatch_rs<NEURON, 1, GM_FOLD12>(rs, gt, a, b, s);
-    } else if (gm == GM_FOLD) {
-        if (vec == 2) bwd_dispatch_rs<NEURON, 2, GM_FOLD>(rs, gt, a, b, s);
-        else bwd_dispatch_rs<NEURON, 1, GM_FOLD>(rs, gt, a, b, s);
-    } else {
-        if (vec == 2) bwd_dispatch_rs<NEURON, 2, GM_FULL>(rs, gt, a, b, s);
-        else bwd_dispatch_rs<NEURON, 1, GM_FULL>(rs, gt, a, b, s);
-    }
 }
 
 }  // namespace
@@ -833,9 +417,9 @@ hipError_t launch_neuron_bwd(int neuron, int reset_surrogate, int T, int64_t C, 
                        dcur_t_planes, dscale, colsum, dvcol};
     const int rs = reset_surrogate, gt = grad_dtype;
     switch (neuron) {
-        case SNN_SYNAPTIC: bwd_dispatch<SNN_SYNAPTIC>(vec, rs, gm, gt, a, b, s); break;
-        case SNN_RLEAKY: bwd_dispatch<SNN_RLEAKY>(vec, rs, gm, gt, a, b, s); break;
-        default: bwd_dispatch<SNN_LEAKY>(vec, rs, gm, gt, a, b, s);
+        case SNN_SYNAPTIC: scan_bwd_synaptic(vec, rs, gm, gt, a, b, s); break;
+        case SNN_RLEAKY: scan_bwd_rleaky(vec, rs, gm, gt, a, b, s); break;
+        default: scan_bwd_leaky(vec, rs, gm, gt, a, b, s);
     }
     return hipGetLastError();
 }

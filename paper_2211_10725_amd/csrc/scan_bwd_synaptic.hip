@@ -1,0 +1,11 @@
+// The reverse scan's instantiations for SNN_SYNAPTIC.
+#include "scan_bwd.hpp"
+
+namespace snn {
+
+void scan_bwd_synaptic(int vec, int rs, int gm, int gt, const ScanArgs &a, const BwdBuffers &b,
+                       hipStream_t s) {
+    bwd_dispatch<SNN_SYNAPTIC>(vec, rs, gm, gt, a, b, s);
+}
+
+}  // namespace snn

@@ -50,12 +50,15 @@ __device__ inline uint32_t bf16_rne_u32(float x) {
     return (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
 }
 __device__ inline void split_bf16x3(float x, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
-    const uint32_t b = __float_as_uint(x);
+    const uint32_t b = __float_as_uint(x), a = b & 0x7fffffffu;
     hi = (b + 0x7fffu + ((b >> 16) & 1u)) >> 16;
-    const bool top = (b & 0x7fffffffu) >= 0x7f7f8000u;  // rounds to infinity, or not finite
-    const bool special = (b & 0x7f800000u) == 0x7f800000u;
-    if (top) hi = (b >> 16) | ((b & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u);
-    const float r = special ? 0.f : x - __uint_as_float(hi << 16);
+    float r = x - __uint_as_float(hi << 16);
+    if (__builtin_expect(__any(a >= 0x7f7f8000u), 0)) {  // rounds to infinity, or not finite
+        if (a >= 0x7f7f8000u) {
+            hi = (b >> 16) | (a > 0x7f800000u ? 0x40u : 0u);
+            r = a >= 0x7f800000u ? 0.f : x - __uint_as_float(hi << 16);
+        }
+    }
     mid = bf16_rne_u32(r);
     lo = bf16_rne_u32(r - __uint_as_float(mid << 16));
 }
