@@ -564,7 +564,8 @@ AsyncPlan plan_async(const GemmArgs &g) {
     const int nk = (g.K + kKT - 1) / kKT;
     int S = 1;
     const int cus = 256;  // one workgroup per CU; MI355X has 256 CUs
-    if (tiles < cus) S = max(1, min(min(cus / tiles, nk / 16), 64));
+    const int parts = g.b_dtype == SNN_F32 ? 3 : 1;  // (gemm_async_sum_chunk)
+    if (tiles < cus) S = max(1, min(min(cus / tiles, parts * nk / 16), 64));
     const int per = (nk + S - 1) / S;
     p.k_chunk = per * kKT;
     p.splits = (g.K + p.k_chunk - 1) / p.k_chunk;
@@ -587,24 +588,49 @@ double async_us(const GemmArgs &g, const AsyncPlan &p) {
 
 }  // namespace
 
-bool gemm_async_applies(const GemmArgs &g) {
+namespace {
+// sizes that 256 x 256 tiles of these layouts take
+bool fits_async(const GemmArgs &g) {
     // both operands K-contiguous, or both M/N-contiguous
     if (!g.allow_split || g.a_kc != g.b_kc) return false;
-    if (mfma_type(g.a_dtype, g.b_dtype) < 0) return false;
     if (g.K % 8 != 0 || g.K < 256 || g.M < kTile || g.N < kTile) return false;
     if (g.bias && g.N > kBiasLds) return false;
     if (!g.a_kc && (g.M % 8 != 0 || g.N % 8 != 0)) return false;
-    if (g.a_dtype != SNN_U8 && g.lda % 8 != 0) return false;
-    if (g.b_dtype != SNN_U8 && g.ldb % 8 != 0) return false;
     // large enough to fill the device with 256 x 256 tiles (K split as needed)
-    if ((double)g.M * g.N * g.K < 1073741824.0) return false;
+    return (double)g.M * g.N * g.K >= 1073741824.0;
+}
+bool aligned_rows(int dtype, int64_t ld) { return dtype == SNN_U8 || ld % 8 == 0; }
+}  // namespace
+
+bool gemm_async_applies(const GemmArgs &g) {
+    if (!fits_async(g) || mfma_type(g.a_dtype, g.b_dtype) < 0) return false;
+    if (!aligned_rows(g.a_dtype, g.lda) || !aligned_rows(g.b_dtype, g.ldb)) return false;
     return async_us(g, plan_async(g)) <= gemm_joint_us(g);
+}
+
+int gemm_async_sum_chunk(const GemmArgs &g) {
+    if (!fits_async(g)) return 0;
+    const AsyncPlan p = plan_async(g);
+    if (g.b_dtype == SNN_F32)  // three passes: sizes that fill the device with items
+        return (g.a_dtype == SNN_U8 || g.a_dtype == SNN_BF16) &&
+                       p.tiles_m * p.tiles_n * p.splits >= 192 &&
+                       (double)g.M * g.N * g.K >= 4294967296.0
+                   ? p.k_chunk
+                   : 0;
+    if (mfma_type(g.a_dtype, g.b_dtype) < 0 || !aligned_rows(g.a_dtype, g.lda) ||
+        !aligned_rows(g.b_dtype, g.ldb))
+        return 0;
+    return p.k_chunk;
 }
 
 size_t gemm_async_workspace_bytes(const GemmArgs &g) {
     if (!gemm_async_applies(g)) return 0;
     const AsyncPlan p = plan_async(g);
-    return p.a_bytes + p.b_bytes + p.part_bytes;
+    const size_t own = p.a_bytes + p.b_bytes + p.part_bytes;
+    // asked without a bias, which takes layers this wide to the other kernels
+    if (!g.bias && g.a_kc && g.N > kBiasLds)
+        return max(own, max(gemm_joint_workspace_bytes(g), gemm16_workspace_bytes(g)));
+    return own;
 }
 
 hipError_t launch_gemm_async(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s) {

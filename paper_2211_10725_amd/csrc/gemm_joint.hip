@@ -95,15 +95,16 @@ __device__ inline int kc_swz(int r) {
 }
 __device__ inline int mn_swz(int k) { return 2 * ((k & 3) | ((k & 1) << 2)); }
 
-// The part products of a k16 step, smallest first.  Spikes by three parts keep
-// two sums, lo and mid in one, hi in the other, added at the end: the hi
-// products are 8-bit numbers whose sums are mostly exact in fp32, while
-// adding all three parts into one sum rounds three times per step at full
-// magnitude (2.4e-7 against 4.6e-8 of the result's rms over K = 784).
+// The part products of a k16 step, smallest first.  Three parts by spikes (a
+// weight gradient) keep two sums, lo and mid in one, hi in the other, added at
+// the end: the hi products are 8-bit numbers whose sums are mostly exact in
+// fp32, while adding all three parts into one sum rounds three times per step
+// at full magnitude (2.4e-7 against 4.6e-8 of the result's rms over K = 784).
+// The currents (spikes by three parts) keep one sum: see sum_order().
 template <int PA, int PB>
 struct Products {
     static constexpr int kCount = PA * PB == 9 ? 6 : PA * PB;
-    static constexpr int kSums = PA * PB == 3 ? 2 : 1;
+    static constexpr int kSums = PA == 3 && PB == 1 ? 2 : 1;
     static constexpr int a(int q) {
         if (PA * PB == 9) {
             constexpr int t[6] = {2, 1, 0, 1, 0, 0};
@@ -273,6 +274,7 @@ __device__ inline void static_for(const Fn &f) {
 
 struct JointArgs {
     int M, N, K, k_chunk, tiles_n, tiles, total;
+    int sum_chunk;  // FOLD: K is summed in chunks of this length, added in order
     const uint16_t *A, *B;
     int64_t lda, ldb, a_ps, b_ps;
     int a_cols, b_cols;
@@ -331,6 +333,11 @@ constexpr int waves_per_simd() {
     return NW == 8 || R * (PA * BM + PB * BN) * KT * 2 <= 76 * 1024 ? 2 : 1;
 }
 
+// NP = 3: B's parts are taken in turn, all k-tiles of a chunk with lo, then
+// with mid, then with hi.  FOLD: the sum over each chunk of K starts from
+// zero and is added to the total (the order of a split K whose partials are
+// added in turn, without writing the partials).
+//
 // The k-tiles of a workgroup's items, item after item, run through a ring of
 // R LDS slots; step t multiplies the tile in slot t % R.  With R >= 3, at the
 // barrier that opens a step every wave has finished reading slot (t - 1) % R
@@ -340,7 +347,8 @@ constexpr int waves_per_simd() {
 // LDS reads across the barrier.  With R = 2 the barrier only gives tile t,
 // and the step copies tile t + 1.  The next item's first tiles are copied by
 // the current item's last steps and are in flight during its stores.
-template <int MT, int PA, int PB, int LA, int LB, int BM, int BN, int KT, int R, int WM, int WN>
+template <int MT, int PA, int PB, int LA, int LB, int BM, int BN, int KT, int R, int WM, int WN,
+          int NP, bool FOLD>
 __global__ __launch_bounds__(64 * WM * WN, (waves_per_simd<PA, PB, BM, BN, KT, R, WM * WN>()))
 void gemm_joint_kernel(JointArgs g) {
     constexpr int NW = WM * WN;
@@ -380,7 +388,7 @@ void gemm_joint_kernel(JointArgs g) {
     TB tb;
     int cj = 0, citem = item, cslot = 0;
     Item ci = locate<BM, BN>(g, citem);
-    int ck = ci.kbeg;
+    int ck = ci.kbeg, cbeg = ci.kbeg, cplane = NP - 1;  // k-tile, its chunk's start, B's part
     auto copy_setup = [&] {
         ta.init((uint32_t)g.lda, g.M, g.a_cols, ci.m0);
         tb.init((uint32_t)g.ldb, g.N, g.b_cols, ci.n0);
@@ -402,17 +410,28 @@ void gemm_joint_kernel(JointArgs g) {
         } else if constexpr (piece() == 1) {
 #pragma unroll
             for (int p = 0; p < PB; ++p)
-                tb.copy(g.B + p * g.b_ps, (uint32_t)g.ldb, g.b_cols, g.K, ck,
+                tb.copy(g.B + (p + (NP > 1 ? cplane : 0)) * g.b_ps, (uint32_t)g.ldb, g.b_cols, g.K, ck,
                         to + kOffB + p * TB::kPlane);
         } else {
             ++ahead;
             cslot = cslot + 1 == R ? 0 : cslot + 1;
             ck += KT;
+            if constexpr (NP > 1) {
+                if (ck >= min(cbeg + g.sum_chunk, ci.kend)) {
+                    if (cplane > 0) {
+                        --cplane;
+                        ck = cbeg;
+                    } else {
+                        cplane = NP - 1;
+                        cbeg = ck;
+                    }
+                }
+            }
             if (ck >= ci.kend) {
                 citem = persistent_item(blockIdx.x, gridDim.x, g.total, ++cj);
                 if (citem >= 0) {
                     ci = locate<BM, BN>(g, citem);
-                    ck = ci.kbeg;
+                    ck = cbeg = ci.kbeg;
                     copy_setup();
                 }
             }
@@ -429,9 +448,11 @@ void gemm_joint_kernel(JointArgs g) {
 
     for (int j = 0; item >= 0; ++j) {
         const Item it = locate<BM, BN>(g, item);
-        floatx16 acc[PR::kSums][FM][FN];
+        static_assert(!FOLD || PR::kSums == 1, "the second sum is the total");
+        constexpr int kAcc = FOLD ? 2 : PR::kSums;
+        floatx16 acc[kAcc][FM][FN];
 #pragma unroll
-        for (int z = 0; z < PR::kSums; ++z)
+        for (int z = 0; z < kAcc; ++z)
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -439,7 +460,22 @@ void gemm_joint_kernel(JointArgs g) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[z][i][q][r] = 0.f;
         if constexpr (kCross) read_all(slot * kSlot);
-        for (int k0 = it.kbeg; k0 < it.kend; k0 += KT) {
+        int plane = NP - 1, beg = it.kbeg;
+        for (int k0 = it.kbeg, nk; k0 < it.kend; k0 = nk) {
+            nk = k0 + KT;
+            bool chunk_done = false;
+            if constexpr (NP > 1 || FOLD) {
+                if (nk >= min(beg + g.sum_chunk, it.kend)) {
+                    if (plane > 0) {
+                        --plane;
+                        nk = beg;
+                    } else {
+                        plane = NP - 1;
+                        beg = nk;
+                        chunk_done = true;
+                    }
+                }
+            }
             // The tile this barrier gives (t + 1, or t for R = 2) has landed;
             // the tiles after it may be in flight.  A whole tile's stores were
             // issued after every copy that the next steps wait for, and vector
@@ -453,7 +489,7 @@ void gemm_joint_kernel(JointArgs g) {
                 asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
             ++since_stores;
             const int kvalid = it.kend - k0;
-            const bool more = k0 + KT < it.kend;
+            const bool more = nk < it.kend;
             const uint32_t d = slot * kSlot;
             const int ns = slot + 1 == R ? 0 : slot + 1;
             const uint32_t dn = more ? ns * kSlot : d;
@@ -497,6 +533,17 @@ void gemm_joint_kernel(JointArgs g) {
             });
             slot = ns;
             --ahead;
+            if (FOLD && chunk_done) {
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int q = 0; q < FN; ++q)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            acc[kAcc - 1][i][q][r] += acc[0][i][q][r];
+                            acc[0][i][q][r] = 0.f;
+                        }
+            }
         }
         if constexpr (kCross) {
             // the reads past the last tile land before their registers are
@@ -530,7 +577,7 @@ void gemm_joint_kernel(JointArgs g) {
             for (int q = 0; q < FN; ++q) {
                 const int n = it.n0 + (wn * FN + q) * 32 + (lane & 31);
                 const int mb = it.m0 + (wm * FM + i) * 32 + 4 * (lane >> 5);
-                floatx16 v = acc[0][i][q];
+                floatx16 v = acc[FOLD ? 1 : 0][i][q];
                 if constexpr (PR::kSums == 2) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) v[r] += acc[PR::kSums - 1][i][q][r];
@@ -700,13 +747,14 @@ struct Operand {
 };
 
 // frag: the operand may be packed in fragment order (K-contiguous operands
-// that are rewritten anyway: 1 KiB of consecutive memory per copy)
-Operand plan_operand(int dtype, bool kc, int64_t ld, int64_t ps, int rows, int K, bool frag) {
+// that are rewritten anyway, or `always`: 1 KiB of consecutive memory per copy)
+Operand plan_operand(int dtype, bool kc, int64_t ld, int64_t ps, int rows, int K, bool frag,
+                     bool always) {
     Operand o{};
     const int mr = kc ? rows : K, mc = kc ? K : rows;  // memory rows, columns
     o.rows = mr;
     o.layout = kc ? L_KC : L_MN;
-    o.pack = dtype == SNN_U8 || dtype == SNN_F32 || mc % 8 != 0 || ld % 8 != 0 ||
+    o.pack = always || dtype == SNN_U8 || dtype == SNN_F32 || mc % 8 != 0 || ld % 8 != 0 ||
              (dtype == kPlanes3 && ps % 8 != 0);
     o.cols = (mc + 7) / 8 * 8;
     o.ld = o.pack ? o.cols : ld;
@@ -721,7 +769,7 @@ Operand plan_operand(int dtype, bool kc, int64_t ld, int64_t ps, int rows, int K
 }
 
 // Tile configurations: tile, k-tile, ring slots, items per CU at once
-enum : int { kNone = 0, kOne, kThree, kThreeT, kNineBig, kNineSmall };
+enum : int { kNone = 0, kOne, kThree, kThreeT, kNineBig, kNineSmall, kTurnBig, kTurn, kThreeSmall };
 struct Shape { int BM, BN, KT, R, per_cu; float step_us; };
 // Time of one k-tile step of one item with the CU's other items beside it, from
 // contractions of 2013 .. 16000 rows with 700 .. 2048 inputs and outputs.  Two
@@ -736,10 +784,13 @@ constexpr Shape kShapes[] = {{0, 0, 0, 0, 0, 0.f},
                              {256, 128, 32, 3, 1, 1.3f},
                              {128, 256, 32, 3, 1, 1.3f},
                              {256, 128, 32, 2, 1, 2.8f},
-                             {128, 128, 32, 3, 1, 1.6f}};
+                             {128, 128, 32, 3, 1, 1.6f},
+                             {256, 256, 64, 2, 1, 1.8f},
+                             {256, 128, 64, 3, 1, 1.1f},
+                             {128, 128, 32, 3, 1, 0.75f}};
 
 struct JointPlan {
-    int cfg, mt, tiles_m, tiles_n, splits, k_chunk;
+    int cfg, mt, tiles_m, tiles_n, splits, k_chunk, sum_chunk;
     Operand a, b;
     size_t part_bytes;
     double us;  // estimated kernel time (with the reduction of split partials)
@@ -771,37 +822,94 @@ void plan_cfg(const GemmArgs &g, int cfg, JointPlan &best) {
     }
 }
 
+// The order in which a product of two K-contiguous operands, the currents, is
+// summed.  A membrane within rounding of the threshold turns a spike with the
+// last bit of its current, so kernels that take over a size keep the order
+// that it is summed in by the others, bit for bit: where 256 x 256 tiles fill
+// the device (gemm_async_sum_chunk), its chunks of K, an fp32 operand's parts in
+// turn over each; else the 16-bit kernel's chunks, the parts in turn at each
+// k16 step.
+struct SumOrder {
+    int chunk;
+    bool turn;
+};
+SumOrder sum_order(const GemmArgs &g) {
+    GemmArgs o = g;
+    if (fp32ish(g.b_dtype)) o.a_dtype = SNN_U8;  // bf16 spikes as the bytes they stand for
+    SumOrder r{};
+    r.chunk = gemm_async_sum_chunk(o);
+    r.turn = r.chunk > 0 && fp32ish(g.b_dtype);
+    if (r.chunk == 0) r.chunk = gemm16_sum_chunk(o);
+    if (r.chunk == 0) r.chunk = g.K;
+    return r;
+}
+
+// Currents: the chunks of the order summed by one workgroup in turn, or one
+// item each with their partials added by the reduction (the wide reduction of
+// 16 or more adds quarters: only the split takes its order).
+void plan_order(const GemmArgs &g, int cfg, bool fold, const SumOrder &o, JointPlan &best) {
+    const Shape &sh = kShapes[cfg];
+    const int tm = (g.M + sh.BM - 1) / sh.BM, tn = (g.N + sh.BN - 1) / sh.BN;
+    const int chunks = (g.K + o.chunk - 1) / o.chunk, slots = 256 * sh.per_cu;
+    const int passes = o.turn ? 3 : 1;
+    for (const int S : {1, chunks}) {
+        if (S == 1 && chunks > 1 && (!fold || chunks >= 16)) continue;
+        const int span = S == 1 ? g.K : o.chunk;
+        const int64_t rounds = ((int64_t)tm * tn * S + slots - 1) / slots;
+        double us = rounds * (passes * ((span + sh.KT - 1) / sh.KT) * (double)sh.step_us + 3.0);
+        if (S > 1) us += 4.0 + (double)g.M * g.N * 4.0 * (2 * S + 1) / 4.5e6;
+        if (us < best.us) {
+            best.us = us;
+            best.cfg = cfg;
+            best.tiles_m = tm;
+            best.tiles_n = tn;
+            best.splits = S;
+            best.k_chunk = S == 1 ? (g.K + 63) / 64 * 64 : o.chunk;
+            best.sum_chunk = o.chunk;
+        }
+    }
+}
+
 JointPlan make_plan(const GemmArgs &g) {
     JointPlan p{};
     p.us = 1e300;
     p.mt = pair_type(g.a_dtype, g.b_dtype);
     const int pa = fp32ish(g.a_dtype) ? 3 : 1, pb = fp32ish(g.b_dtype) ? 3 : 1;
-    const bool frag = pa * pb == 3 && g.a_kc && g.b_kc;
-    p.a = plan_operand(g.a_dtype, g.a_kc, g.lda, g.a_ps, g.M, g.K, frag && g.a_dtype == SNN_U8);
-    p.b = plan_operand(g.b_dtype, g.b_kc, g.ldb, g.b_ps, g.N, g.K, frag);
+    const bool currents = g.a_kc && g.b_kc;
+    const SumOrder o = currents ? sum_order(g) : SumOrder{};
+    const bool frag = pa * pb == 3 && currents;
+    // (taking the parts in turn, both come in fragment order)
+    p.a = plan_operand(g.a_dtype, g.a_kc, g.lda, g.a_ps, g.M, g.K,
+                       frag && (g.a_dtype == SNN_U8 || o.turn), frag && o.turn);
+    p.b = plan_operand(g.b_dtype, g.b_kc, g.ldb, g.b_ps, g.N, g.K, frag, false);
     if (pa * pb == 9) {
         plan_cfg(g, kNineBig, p);
         plan_cfg(g, kNineSmall, p);
-    } else if (pa * pb == 3) {
-        plan_cfg(g, g.a_kc ? kThree : kThreeT, p);
+    } else if (o.turn) {
+        plan_order(g, kTurnBig, false, o, p);
+        plan_order(g, kTurn, true, o, p);
+    } else if (currents) {
+        plan_order(g, pb == 3 ? kThree : kOne, true, o, p);
+        if (pb == 3) plan_order(g, kThreeSmall, true, o, p);
     } else {
-        plan_cfg(g, kOne, p);
+        plan_cfg(g, pa == 3 ? kThreeT : kOne, p);
     }
     p.part_bytes = p.splits > 1 ? align_up((size_t)p.splits * g.M * g.N * sizeof(float)) : 0;
     return p;
 }
 
-template <int MT, int PA, int PB, int LA, int LB, int CFG, int WM, int WN>
+template <int MT, int PA, int PB, int LA, int LB, int CFG, int WM, int WN, int NP = 1,
+          bool FOLD = false>
 void launch_cfg(const JointArgs &a, hipStream_t s) {
     constexpr Shape sh = kShapes[CFG];
     const unsigned grid = (unsigned)min(a.total, device_cus() * sh.per_cu);
-    gemm_joint_kernel<MT, PA, PB, LA, LB, sh.BM, sh.BN, sh.KT, sh.R, WM, WN>
+    gemm_joint_kernel<MT, PA, PB, LA, LB, sh.BM, sh.BN, sh.KT, sh.R, WM, WN, NP, FOLD>
         <<<grid, 64 * WM * WN, 0, s>>>(a);
 }
 
 template <int MT>
 void launch_one(const GemmArgs &g, const JointArgs &a, hipStream_t s) {
-    if (g.a_kc && g.b_kc) launch_cfg<MT, 1, 1, L_KC, L_KC, kOne, 2, 2>(a, s);
+    if (g.a_kc && g.b_kc) launch_cfg<MT, 1, 1, L_KC, L_KC, kOne, 2, 2, 1, true>(a, s);
     else if (g.a_kc) launch_cfg<MT, 1, 1, L_KC, L_MN, kOne, 2, 2>(a, s);
     else launch_cfg<MT, 1, 1, L_MN, L_MN, kOne, 2, 2>(a, s);
 }
@@ -813,7 +921,7 @@ bool gemm_joint_applies(const GemmArgs &g) {
     if (pair_type(g.a_dtype, g.b_dtype) < 0) return false;
     if (!g.a_kc && g.b_kc) return false;
     if (g.a_dtype == kPlanes3 &&
-        plan_operand(kPlanes3, g.a_kc, g.lda, g.a_ps, g.M, g.K, false).pack)
+        plan_operand(kPlanes3, g.a_kc, g.lda, g.a_ps, g.M, g.K, false, false).pack)
         return false;
     if (g.b_dtype == kPlanes3) return false;
     const bool nine = fp32ish(g.a_dtype) && fp32ish(g.b_dtype);
@@ -835,10 +943,25 @@ double gemm_joint_us(const GemmArgs &g) {
     return gemm_joint_applies(g) ? make_plan(g).us : 1e300;
 }
 
+namespace {
+size_t gemm_order_part_bytes(const GemmArgs &g) {
+    GemmArgs o = g;
+    if (fp32ish(g.b_dtype)) o.a_dtype = SNN_U8;
+    const int chunk = gemm_async_sum_chunk(o);
+    const size_t turn = chunk > 0 && chunk < g.K
+                            ? align_up((size_t)((g.K + chunk - 1) / chunk) * g.M * g.N * sizeof(float))
+                            : 0;
+    return max(turn, gemm16_workspace_bytes(o));
+}
+}  // namespace
+
 size_t gemm_joint_workspace_bytes(const GemmArgs &g) {
     if (!gemm_joint_applies(g)) return 0;
     const JointPlan p = make_plan(g);
-    return p.a.bytes + p.b.bytes + p.part_bytes;
+    size_t part = p.part_bytes;
+    // the chunks may depend on the device and on a bias: any plan's partials
+    if (g.a_kc && g.b_kc) part = max(part, gemm_order_part_bytes(g));
+    return p.a.bytes + p.b.bytes + part;
 }
 
 hipError_t launch_gemm_joint(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s) {
@@ -849,6 +972,7 @@ hipError_t launch_gemm_joint(const GemmArgs &g, void *ws, size_t ws_bytes, hipSt
     JointArgs a{};
     a.M = g.M; a.N = g.N; a.K = g.K;
     a.k_chunk = p.k_chunk;
+    a.sum_chunk = p.sum_chunk;
     a.tiles_n = p.tiles_n;
     a.tiles = p.tiles_m * p.tiles_n;
     a.total = a.tiles * p.splits;
@@ -899,9 +1023,19 @@ hipError_t launch_gemm_joint(const GemmArgs &g, void *ws, size_t ws_bytes, hipSt
         case kNineBig: launch_cfg<MT_BF16, 3, 3, L_KC, L_MN, kNineBig, 4, 2>(a, s); break;
         case kNineSmall: launch_cfg<MT_BF16, 3, 3, L_KC, L_MN, kNineSmall, 2, 4>(a, s); break;
         case kThree:
-            if (p.a.layout == L_PK) launch_cfg<MT_BF16, 1, 3, L_PK, L_PK, kThree, 4, 2>(a, s);
-            else launch_cfg<MT_BF16, 1, 3, L_KC, L_PK, kThree, 4, 2>(a, s);
+            if (p.a.layout == L_PK)
+                launch_cfg<MT_BF16, 1, 3, L_PK, L_PK, kThree, 4, 2, 1, true>(a, s);
+            else
+                launch_cfg<MT_BF16, 1, 3, L_KC, L_PK, kThree, 4, 2, 1, true>(a, s);
             break;
+        case kThreeSmall:
+            if (p.a.layout == L_PK)
+                launch_cfg<MT_BF16, 1, 3, L_PK, L_PK, kThreeSmall, 4, 2, 1, true>(a, s);
+            else
+                launch_cfg<MT_BF16, 1, 3, L_KC, L_PK, kThreeSmall, 4, 2, 1, true>(a, s);
+            break;
+        case kTurnBig: launch_cfg<MT_BF16, 1, 1, L_PK, L_PK, kTurnBig, 2, 4, 3>(a, s); break;
+        case kTurn: launch_cfg<MT_BF16, 1, 1, L_PK, L_PK, kTurn, 4, 2, 3, true>(a, s); break;
         case kThreeT: launch_cfg<MT_BF16, 3, 1, L_MN, L_MN, kThreeT, 2, 4>(a, s); break;
         default:
             if (p.mt == MT_F16) launch_one<MT_F16>(g, a, s);

@@ -879,6 +879,18 @@ size_t gemm16_workspace_bytes(const GemmArgs &g) {
     return best;
 }
 
+int gemm16_sum_chunk(const GemmArgs &g) {
+    const Kind kd = classify(g.a_dtype, g.b_dtype);
+    if (!kd.ok || !g.a_kc || !g.b_kc) return 0;
+    if (kd.mt == MT_BF16 && kd.sa == SRC_SPIKE && kd.sb == SRC_F32)
+        return plan_for<MT_BF16, SRC_SPIKE, true, SRC_F32, true>(g, kd).k_chunk;
+    if (kd.mt == MT_F16 && kd.sa == SRC_SPIKE && kd.sb == SRC_H16)
+        return plan_for<MT_F16, SRC_SPIKE, true, SRC_H16, true>(g, kd).k_chunk;
+    if (kd.mt == MT_F16 && kd.sa == SRC_H16 && kd.sb == SRC_H16)
+        return plan_for<MT_F16, SRC_H16, true, SRC_H16, true>(g, kd).k_chunk;
+    return 0;
+}
+
 hipError_t launch_gemm16(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s) {
     const Kind kd = classify(g.a_dtype, g.b_dtype);
     bool sup = false;

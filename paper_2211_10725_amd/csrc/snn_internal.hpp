@@ -164,6 +164,8 @@ hipError_t launch_divide(int M, int N, float *C, int64_t ldc, const float *c_div
 bool gemm16_applies(const GemmArgs &g);
 size_t gemm16_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm16(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
+// length of the chunks of K that its plan sums one by one (0: not applicable)
+int gemm16_sum_chunk(const GemmArgs &g);
 int gemm16_passes(const GemmArgs &g);  // MFMA passes per product, 0 if not applicable
 // dst[p][rows][ldp] = part p (hi, mid, lo) of the exact three-bf16 split of
 // src[r * ld + k], k < K; columns K .. ldp - 1 are 0
@@ -186,6 +188,9 @@ hipError_t launch_narrow_fwd(const GemmArgs &g, hipStream_t s);
 
 // ---- large single-part contractions, asynchronous LDS pipeline (gemm_async.hip)
 bool gemm_async_applies(const GemmArgs &g);
+// length of the chunks of K that 256 x 256 tiles sum one by one where they fill
+// the device (0: they do not); an fp32 B counts as three passes
+int gemm_async_sum_chunk(const GemmArgs &g);
 size_t gemm_async_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm_async(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
 

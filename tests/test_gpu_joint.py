@@ -115,3 +115,23 @@ def test_input_gradient_of_special_values(bad, from_planes):
     assert torch.equal(gx[torch.isinf(ref)], ref[torch.isinf(ref)])
     tol = (6 * n_out + 6) * 2.0 ** -24 * (dI[:, :].double().abs() @ W.double().abs())
     assert bool(((gx.double() - ref.double()).abs()[fin] <= tol[fin]).all())
+
+
+# parts in turn: one 256 x 256 item per tile; chunks of K folded by a workgroup;
+# one wave of 128 x 128 tiles against 256 x 128 ones, with one chunk and several
+@pytest.mark.parametrize("M,n_in,n_out", [(12801, 784, 1000), (6401, 1000, 1001), (2013, 1003, 1101),
+                                          (1500, 2001, 600), (9000, 1001, 520)])
+@pytest.mark.parametrize("bytes_in", [True, False])
+def test_currents_in_the_kept_order(M, n_in, n_out, bytes_in):
+    """The currents of every plan of the kept order of summation, spikes as
+    bytes and as bf16 values, every row and column of the last tiles."""
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, M)
+    if not bytes_in:
+        d.in_dtype = snn.BF16
+        x = x.bfloat16()
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    cur = torch.full((M, n_out), float("nan"), device="cuda")
+    snn.snn_synapse_fwd(d, x, W, b, cur, None, ws)
+    xd, Wd = x.double(), W.double()
+    _within(cur, xd @ Wd.t() + b.double(), xd @ Wd.abs().t() + b.double().abs(), 3 * n_in + 1, 0.0,
+            "currents")
