@@ -39,6 +39,8 @@
 // bytes; an fp32 dC^T is written directly as three exact bf16 planes when the
 // weight gradient runs on the 16-bit cores.  The bias gradient comes from the
 // neuron scan's per-column sums.
+#include <atomic>
+
 #include "snn_internal.hpp"
 
 namespace snn {
@@ -636,6 +638,230 @@ __global__ __launch_bounds__(kDxThreads) void conv_dx_kernel(
     }
 }
 
+// ---- input gradient of wider layers and larger images ---------------------------
+// The same product for layers that conv_dx_kernel does not take (up to 36
+// pooled cells, 96 output channels, any number of input channels): a workgroup
+// takes a group of at most 10 input channels, keeps their weights in registers
+// as three bf16 parts, and goes through its share of the images, two halves of
+// at most 5 channels (125 of 128 columns) each:
+//   dC of the image in LDS as three parts ([part][m][co], staged while the
+//   previous image's columns are gathered), all column tiles of both halves
+//   accumulated from one read of the dC fragments, then half by half dcol^T
+//   through LDS and the gather of col2im_kernel (fixed order ky, kx).
+// Wave v takes column tile v of each half and every row tile (RT of 16 window
+// rows); KSN k-steps of 32 output channels.  Six of the nine part products, as
+// conv_dx_kernel.  An infinity or NaN leaves NaN against zero parts: such a
+// value of dcol is taken again from the whole values.
+//
+// What bounds it: the matrix cores in the products (six bf16 passes), the LDS
+// pipe in the gather; the two alternate in each workgroup, one per compute
+// unit.  The contraction and gather through HBM that it replaces moved 4 bytes
+// x 25 x Ci per window row both ways and ran the products on fp32 MFMA.
+// 1600 images of 32 x 14 x 14 to 64 channels: 452 -> 182 us (the products of
+// full tiles would take about 70 at the contractions' rate); 2400 of 48 x 9 x 9 to
+// 16, forward and both gradients 358 -> 252 us.
+constexpr int kDxwMaxCells = 36;
+constexpr int kDxwMaxCo = 96;
+constexpr int kDxwHalf = 5;                     // channels of a half: 125 of 128 columns
+constexpr size_t kDxwMaxLds = 160 * 1024 - 256;
+constexpr int dxw_ldm(int RT) { return RT * 16 + 4; }   // dcol^T row stride (floats) and
+constexpr int dxw_ldc(int KSN) { return KSN * 32 + 8; } // dC part row stride (bf16): 16 lanes'
+                                                        // 16-byte accesses on distinct banks
+constexpr size_t dxw_lds(int RT, int KSN) {
+    return (size_t)128 * dxw_ldm(RT) * 4 + (size_t)3 * RT * 16 * dxw_ldc(KSN) * 2;
+}
+
+template <int RT, int KSN>
+__global__ __launch_bounds__(kDxThreads) void conv_dx_wide_kernel(
+    int NB, int Ci, int H, int W, int Co, int Hp, int Wp, int groups, int cpg,
+    const float *__restrict__ dI, const uint8_t *__restrict__ arg, const float *__restrict__ w,
+    float *__restrict__ dx) {
+    constexpr int LDM = dxw_ldm(RT), LDC = dxw_ldc(KSN), PART = RT * 16 * LDC;
+    constexpr int kPer = (KSN * 16 * RT * 4 + kDxThreads - 1) / kDxThreads;  // (co pair, q)
+    extern __shared__ __attribute__((aligned(16))) char dxw_smem[];
+    float *dcol = reinterpret_cast<float *>(dxw_smem);
+    uint16_t *dcp = reinterpret_cast<uint16_t *>(dxw_smem + (size_t)128 * LDM * 4);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int col = lane & 15, kg = lane >> 4;
+    const int HW = Hp * Wp, Kc = Ci * KS * KS, CHW = Co * HW;
+    const int grp = blockIdx.x % groups, c0 = grp * cpg, nc = min(cpg, Ci - c0);
+    const int first = blockIdx.x / groups, step = gridDim.x / groups;
+    const int hc = cpg > kDxwHalf ? (cpg + 1) / 2 : cpg;  // channels of the first half
+    const int nch[2] = {min(hc, nc), max(0, nc - hc)};
+
+    // rows past 4 HW and columns past Co stay zero for the whole launch, and so
+    // do dcol^T's padding columns, which a tap outside the windows reads
+    for (int i = tid; i < 3 * PART / 2; i += kDxThreads) reinterpret_cast<uint32_t *>(dcp)[i] = 0u;
+    for (int i = tid; i < 128 * 4; i += kDxThreads) dcol[(i >> 2) * LDM + RT * 16 + (i & 3)] = 0.f;
+
+    // gather: thread (cg, p) takes pixel p of channels cg + G j of a half
+    const int HWi = H * W, npix = Ci * HWi, G = kDxThreads / HWi;
+    const bool gact = tid < G * HWi;
+    const int cg = gact ? tid / HWi : 0, pix = gact ? tid - cg * HWi : 0;
+    int tap[KS * KS];
+    {
+        const int y = pix / W, xx = pix - (pix / W) * W;
+#pragma unroll
+        for (int ky = 0; ky < KS; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < KS; ++kx) {
+                const int oy = y - ky, ox = xx - kx;
+                const bool ok = oy >= 0 && oy < 2 * Hp && ox >= 0 && ox < 2 * Wp;
+                const int m = ok ? 4 * ((oy >> 1) * Wp + (ox >> 1)) + 2 * (oy & 1) + (ox & 1)
+                                 : RT * 16;
+                tap[ky * KS + kx] = (ky * KS + kx) * LDM + m;
+            }
+    }
+
+    // B fragments: lane (col, kg) holds w[32 ks + 8 kg + e][column 16 wv + col of half j]
+    const int n = wv * 16 + col, cl = n / (KS * KS);
+    u32x4 bw[2][KSN][3];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int ks = 0; ks < KSN; ++ks) {
+            uint32_t h[3][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int co = ks * 32 + 8 * kg + e;
+                const float x = cl < nch[j] && co < Co
+                                    ? w[co * Kc + (c0 + j * hc) * KS * KS + n] : 0.f;
+                split_bf16x3(x, h[0][e], h[1][e], h[2][e]);
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                bw[j][ks][p] = u32x4{h[p][0] | (h[p][1] << 16), h[p][2] | (h[p][3] << 16),
+                                     h[p][4] | (h[p][5] << 16), h[p][6] | (h[p][7] << 16)};
+        }
+
+    // a thread's (co pair, cell) items of an image: output channels 2 cp and
+    // 2 cp + 1 of cell q, channel pairs along the lanes (a thread past the
+    // image writes the padding of row 0)
+    const int pairs = (Co + 1) / 2;
+    int src0[kPer], src1[kPer], dst[kPer];
+    bool on0[kPer], on1[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int i = tid + r * kDxThreads, q = i / pairs, cp = i - q * pairs;
+        on0[r] = q < HW;
+        on1[r] = on0[r] && 2 * cp + 1 < Co;
+        src0[r] = on0[r] ? 2 * cp * HW + q : 0;
+        src1[r] = on1[r] ? src0[r] + HW : 0;
+        dst[r] = on0[r] ? 4 * q * LDC + 2 * cp : KSN * 32;
+    }
+    float g0[kPer], g1[kPer];
+    int a0[kPer], a1[kPer];
+    auto fetch = [&](int nb) {
+        const int o = min(nb, NB - 1) * CHW;
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            g0[r] = dI[o + src0[r]];
+            g1[r] = dI[o + src1[r]];
+            a0[r] = arg[o + src0[r]];
+            a1[r] = arg[o + src1[r]];
+        }
+    };
+    auto stage = [&] {
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            uint32_t h[3], k[3];
+            split_bf16x3(on0[r] ? g0[r] : 0.f, h[0], h[1], h[2]);
+            split_bf16x3(on1[r] ? g1[r] : 0.f, k[0], k[1], k[2]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int o = on0[r] ? dst[r] + d * LDC : dst[r];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<uint32_t *>(dcp + p * PART + o) =
+                        (a0[r] == d ? h[p] : 0u) | (a1[r] == d ? k[p] << 16 : 0u);
+            }
+        }
+    };
+
+    if (first >= NB) return;  // (the same for every wave)
+    fetch(first);
+    lds_barrier();  // the zeroed buffers
+    stage();
+    lds_barrier();
+    for (int nb = first; nb < NB; nb += step) {
+        fetch(nb + step);
+        floatx4 acc[2][RT];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < RT; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        // part products smallest first (mid mid, lo hi, hi lo, mid hi, hi mid, hi hi)
+        constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pb[6] = {1, 0, 2, 0, 1, 0};
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int ks = 0; ks < KSN; ++ks) {
+                u32x4 ap[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    ap[p] = *reinterpret_cast<const u32x4 *>(
+                        dcp + p * PART + (16 * i + col) * LDC + 32 * ks + 8 * kg);
+#pragma unroll
+                for (int t = 0; t < 6; ++t)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[j][i] = mfma_bf16(ap[pa[t]], bw[j][ks][pb[t]], acc[j][i]);
+            }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            bool bad = false;
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bad |= !(__builtin_fabsf(acc[j][i][r]) < INFINITY);
+            if (__builtin_expect(__any(bad), 0)) {
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll 1
+                    for (int r = 0; r < 4; ++r) {
+                        const int m = 16 * i + 4 * kg + r, q = m >> 2, d = m & 3;
+                        float t = 0.f;
+                        if (q < HW && cl < nch[j])
+                            for (int co = 0; co < Co; ++co) {
+                                const int o = nb * CHW + co * HW + q;
+                                t = __builtin_fmaf(arg[o] == d ? dI[o] : 0.f,
+                                                   w[co * Kc + (c0 + j * hc) * KS * KS + n], t);
+                            }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (e == r && !(__builtin_fabsf(acc[j][i][e]) < INFINITY))
+                                acc[j][i][e] = t;
+                    }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (nch[j] == 0) break;  // (the same for every wave)
+            // the previous gather is done with dcol, and for j = 0 every
+            // wave's products with dC
+            lds_barrier();
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                *reinterpret_cast<floatx4 *>(dcol + n * LDM + 16 * i + 4 * kg) = acc[j][i];
+            if (j == 0) stage();
+            lds_barrier();
+            if (gact) {
+                float *dxi = dx + (int64_t)nb * npix + (int64_t)(c0 + j * hc) * HWi + pix;
+                for (int c = cg; c < nch[j]; c += G) {
+                    const float *dc = dcol + c * KS * KS * LDM;
+                    float v[KS * KS];
+#pragma unroll
+                    for (int t = 0; t < KS * KS; ++t) v[t] = dc[tap[t]];
+                    float sum = 0.f;
+#pragma unroll
+                    for (int t = 0; t < KS * KS; ++t) sum += v[t];
+                    dxi[c * HWi] = sum;
+                }
+            }
+        }
+    }
+}
+
 // ---- weight gradient in one pass ---------------------------------------------
 // For the same layers up to 32 pooled cells per channel (128 window rows), on
 // spike images of whole 4-byte words: a workgroup takes one image at a time
@@ -837,6 +1063,192 @@ __global__ __launch_bounds__(kDxThreads) void conv_dw_kernel(
             for (int r = 0; r < 4; ++r) {
                 const int co = 16 * i + 4 * kg + r;
                 if (co < Co) out[co * Kc + k] = acc[i][j][r];
+            }
+    }
+}
+
+// ---- weight gradient of wider layers and larger images ---------------------------
+// conv_dw_kernel's product for spike layers of up to 36 pooled cells with any
+// number of channels: a workgroup takes a group of at most 12 input channels
+// (300 of 24 column tiles) and one of at most 64 output channels, and goes
+// through its share of the images, accumulating its block of dW; each
+// workgroup writes its block of the partial sums.  Any image size (spikes are
+// staged byte by byte).
+//
+// What bounds it: the matrix cores (three exact passes) and, about equally, the
+// LDS reads that gather the columns from the image.  col^T and the planes of
+// dC^T through HBM, which it replaces, cost as much as the contraction:
+// 1600 images of 32 x 14 x 14 to 64 channels 215 -> 102 us with the reduction.
+constexpr int kDwwMaxCells = 36;
+constexpr int kDwwMaxCi = 12;
+constexpr int kDwwRows = 160;               // window rows: 5 steps of 32
+constexpr int kDwwLdm = kDwwRows + 8;       // dC^T part row stride (bf16): 336-byte rows
+constexpr int kDwwMaxX = 4096;              // image elements of a group
+constexpr int kDwwXPer = kDwwMaxX / kDxThreads;
+constexpr int kDwwPer = (kDxMaxCo * kDwwMaxCells + kDxThreads - 1) / kDxThreads;
+
+__global__ __launch_bounds__(kDxThreads) void conv_dw_wide_kernel(
+    int NB, int Ci, int H, int W, int Co, int Hp, int Wp, int groups, int cpg, int cogroups,
+    const float *__restrict__ dI, const uint8_t *__restrict__ arg, const uint8_t *__restrict__ x,
+    float *__restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) uint16_t dct[3][kDxMaxCo * kDwwLdm];
+    __shared__ __attribute__((aligned(16))) uint16_t xs[kDwwMaxX];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int col = lane & 15, kg = lane >> 4;
+    const int blk = blockIdx.x % (groups * cogroups), slice = blockIdx.x / (groups * cogroups);
+    const int step = gridDim.x / (groups * cogroups);
+    const int c0 = (blk % groups) * cpg, nc = min(cpg, Ci - c0);
+    const int co0 = (blk / groups) * kDxMaxCo, nco = min(kDxMaxCo, Co - co0);
+    const int HW = Hp * Wp, Kc = Ci * KS * KS, HWi = H * W;
+    const int nd = nco * HW, nx = nc * HWi, kc = nc * KS * KS;
+    const int nms = (4 * HW + 31) / 32;  // 32-row steps of the window rows
+
+    // window rows past 4 HW and channels past the group stay zero for the launch
+    for (int i = tid; i < 3 * kDxMaxCo * kDwwLdm / 2; i += kDxThreads)
+        reinterpret_cast<uint32_t *>(&dct[0][0])[i] = 0u;
+
+    // as conv_dw_kernel: image offsets of a lane's k in each of its tiles, and
+    // corners of its two pooled cells per 32 window rows
+    int koff[3], cb[kDwwRows / 32][2];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int k = (wv + 8 * j) * 16 + col;
+        const int c = k / (KS * KS), t = k - c * KS * KS, ky = t / KS, kx = t - ky * KS;
+        koff[j] = k < kc ? c * HWi + ky * W + kx : 0;
+    }
+#pragma unroll
+    for (int ms = 0; ms < kDwwRows / 32; ++ms)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = 8 * ms + 2 * kg + h, py = q / Wp, px = q - py * Wp;
+            cb[ms][h] = q < HW ? 2 * py * W + 2 * px : 0;
+        }
+    int dst[kDwwPer];  // LDS place of this thread's (co, q) items, -1 past the image
+#pragma unroll
+    for (int r = 0; r < kDwwPer; ++r) {
+        const int i = tid + r * kDxThreads, co = i / HW;
+        dst[r] = i < nd ? co * kDwwLdm + 4 * (i - co * HW) : -1;
+    }
+
+    struct Next {
+        float g[kDwwPer];
+        int a[kDwwPer];
+        uint8_t x[kDwwXPer];
+    };
+    auto fetch = [&](Next &n, int nb) {
+        const int b = min(nb, NB - 1);
+        const float *gp = dI + (int64_t)(b * Co + co0) * HW;
+        const uint8_t *ap = arg + (int64_t)(b * Co + co0) * HW;
+        const uint8_t *xp = x + (int64_t)(b * Ci + c0) * HWi;
+#pragma unroll
+        for (int r = 0; r < kDwwPer; ++r) {
+            const int o = min(tid + r * kDxThreads, nd - 1);
+            n.g[r] = gp[o];
+            n.a[r] = ap[o];
+        }
+#pragma unroll
+        for (int r = 0; r < kDwwXPer; ++r)
+            if (r * kDxThreads < nx) n.x[r] = xp[min(tid + r * kDxThreads, nx - 1)];
+    };
+    auto stage = [&](const Next &n) {
+#pragma unroll
+        for (int r = 0; r < kDwwPer; ++r) {
+            uint32_t pv[3];
+            split_bf16x3(n.g[r], pv[0], pv[1], pv[2]);
+            const int a = n.a[r];
+            if (dst[r] >= 0) {
+#pragma unroll
+                for (int pp = 0; pp < 3; ++pp) {
+                    const uint32_t v = pv[pp];
+                    *reinterpret_cast<uint2 *>(&dct[pp][dst[r]]) =
+                        make_uint2((a == 0 ? v : 0u) | ((a == 1 ? v : 0u) << 16),
+                                   (a == 2 ? v : 0u) | ((a == 3 ? v : 0u) << 16));
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kDwwXPer; ++r) {
+            const int i = tid + r * kDxThreads;
+            if (r * kDxThreads < nx && i < nx)
+                xs[i] = (uint16_t)(__float_as_uint((float)n.x[r]) >> 16);
+        }
+    };
+
+    floatx4 acc[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto products = [&]() {
+#pragma unroll
+        for (int ms = 0; ms < kDwwRows / 32; ++ms) {
+            if (ms < nms) {
+                u32x4 ap[3][4];
+#pragma unroll
+                for (int pp = 0; pp < 3; ++pp)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        ap[pp][i] = *reinterpret_cast<const u32x4 *>(
+                            &dct[pp][(16 * i + col) * kDwwLdm + 32 * ms + 8 * kg]);
+                u32x4 bx[3];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    uint32_t h4[4];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint16_t *q = xs + koff[j] + cb[ms][h];
+                        h4[2 * h] = (uint32_t)q[0] | ((uint32_t)q[1] << 16);
+                        h4[2 * h + 1] = (uint32_t)q[W] | ((uint32_t)q[W + 1] << 16);
+                    }
+                    bx[j] = u32x4{h4[0], h4[1], h4[2], h4[3]};
+                }
+                // parts smallest first
+#pragma unroll
+                for (int pp = 2; pp >= 0; --pp)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j)
+                            acc[i][j] = mfma_bf16(ap[pp][i], bx[j], acc[i][j]);
+            }
+        }
+    };
+
+    // images two ahead in two register sets, as conv_dw_kernel
+    Next n0, n1;
+    int nb = slice;
+    fetch(n0, nb);
+    fetch(n1, nb + step);
+    lds_barrier();  // the zeroed parts
+    stage(n0);
+    lds_barrier();
+    while (true) {
+        fetch(n0, nb + 2 * step);
+        products();
+        lds_barrier();
+        nb += step;
+        if (nb >= NB) break;
+        stage(n1);
+        lds_barrier();
+        fetch(n1, nb + 2 * step);
+        products();
+        lds_barrier();
+        nb += step;
+        if (nb >= NB) break;
+        stage(n0);
+        lds_barrier();
+    }
+    float *out = partial + (int64_t)slice * Co * Kc + (int64_t)co0 * Kc + c0 * KS * KS;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int k = (wv + 8 * j) * 16 + col;
+        if (k >= kc) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int co = 16 * i + 4 * kg + r;
+                if (co < nco) out[co * Kc + k] = acc[i][j][r];
             }
     }
 }
@@ -1086,6 +1498,90 @@ bool dx_one_pass(const ConvGeom &g, bool allow_split) {
            g.Hp * g.Wp <= kDxMaxCells && g.H * g.W <= kDxThreads;
 }
 
+// A handful of images leave the wide kernels with one each and their setup in
+// the open: 8 images of 13 x 8 x 8 to 16 channels, both directions, 42 us with
+// the contractions and 44 with them; 48 x 8 x 8 to 96, 60 and 62.  15 images of
+// 16 x 16 x 16 to 32: 72 and 69.
+constexpr int kWideMinImages = 12;
+
+// the weight gradient by conv_dw_wide_kernel: groups of equal size (groups of
+// input channels x blocks of output channels), and slices of the images
+struct DwWide {
+    bool ok;
+    int groups, cpg, cogroups, slices;
+};
+DwWide dw_wide(const ConvGeom &g, int in_dtype, bool allow_split) {
+    DwWide p{};
+    p.groups = (g.Ci + kDwwMaxCi - 1) / kDwwMaxCi;
+    p.cpg = (g.Ci + p.groups - 1) / p.groups;
+    p.cogroups = (g.Co + kDxMaxCo - 1) / kDxMaxCo;
+    p.slices = max(1, min(g.NB, kDwMaxGrid / (p.groups * p.cogroups)));
+    p.ok = in_dtype == SNN_U8 && allow_split && g.Hp * g.Wp <= kDwwMaxCells &&
+           p.cpg * g.H * g.W <= kDwwMaxX && p.cpg >= 4 &&
+           g.NB >= kWideMinImages;
+    return p;
+}
+
+// row tiles (odd, as instantiated) and k-steps of conv_dx_wide_kernel
+int dxw_rt(const ConvGeom &g) { return (((4 * g.Hp * g.Wp + 15) / 16) | 1); }
+int dxw_ksn(const ConvGeom &g) { return (g.Co + 31) / 32; }
+
+// the input gradient by conv_dx_wide_kernel
+bool dx_wide(const ConvGeom &g, bool allow_split) {
+    return allow_split && !dx_one_pass(g, allow_split) && g.Co <= kDxwMaxCo &&
+           g.Hp * g.Wp <= kDxwMaxCells && g.H * g.W <= kDxThreads &&
+           g.NB >= kWideMinImages && dxw_lds(dxw_rt(g), dxw_ksn(g)) <= kDxwMaxLds;
+}
+
+template <int RT, int KSN>
+hipError_t launch_dx_wide_as(const ConvGeom &g, const float *dI, const uint8_t *arg,
+                             const float *w, float *dx, hipStream_t s) {
+    if constexpr (dxw_lds(RT, KSN) > kDxwMaxLds) {
+        return hipErrorInvalidValue;
+    } else {
+        constexpr size_t lds = dxw_lds(RT, KSN);
+        // groups of equal size, at most two halves; a whole number of
+        // workgroups per group, about one per compute unit
+        const int groups = (g.Ci + 2 * kDxwHalf - 1) / (2 * kDxwHalf);
+        const int cpg = (g.Ci + groups - 1) / groups;
+        const int slices = max(1, min(g.NB, device_cus() / groups));
+        static std::atomic<bool> raised[64];  // per device
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= 64 || !raised[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_dx_wide_kernel<RT, KSN>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            if (dev >= 0 && dev < 64) raised[dev].store(true, std::memory_order_release);
+        }
+        conv_dx_wide_kernel<RT, KSN><<<(unsigned)(groups * slices), kDxThreads, lds, s>>>(
+            g.NB, g.Ci, g.H, g.W, g.Co, g.Hp, g.Wp, groups, cpg, dI, arg, w, dx);
+        return hipGetLastError();
+    }
+}
+
+template <int RT>
+hipError_t launch_dx_wide_rt(const ConvGeom &g, const float *dI, const uint8_t *arg,
+                             const float *w, float *dx, hipStream_t s) {
+    switch (dxw_ksn(g)) {
+        case 1: return launch_dx_wide_as<RT, 1>(g, dI, arg, w, dx, s);
+        case 2: return launch_dx_wide_as<RT, 2>(g, dI, arg, w, dx, s);
+        default: return launch_dx_wide_as<RT, 3>(g, dI, arg, w, dx, s);
+    }
+}
+
+hipError_t launch_dx_wide(const ConvGeom &g, const float *dI, const uint8_t *arg, const float *w,
+                          float *dx, hipStream_t s) {
+    switch (dxw_rt(g)) {
+        case 1: return launch_dx_wide_rt<1>(g, dI, arg, w, dx, s);
+        case 3: return launch_dx_wide_rt<3>(g, dI, arg, w, dx, s);
+        case 5: return launch_dx_wide_rt<5>(g, dI, arg, w, dx, s);
+        case 7: return launch_dx_wide_rt<7>(g, dI, arg, w, dx, s);
+        default: return launch_dx_wide_rt<9>(g, dI, arg, w, dx, s);
+    }
+}
+
 // the forward by conv_fwd_kernel and the weight gradient by conv_dw_kernel
 // (spike input, exact in bf16; up to 32 pooled cells per channel)
 bool dw_one_pass(const ConvGeom &g, int in_dtype, bool allow_split) {
@@ -1140,9 +1636,10 @@ size_t gemm_ws(const GemmArgs &a) {
 struct BwdLayout {
     bool one_pass;  // weight gradient by conv_dw_kernel
     bool small;     // weight gradient by conv_dw_small_kernel
+    DwWide wide;    // weight gradient by conv_dw_wide_kernel
     int chunks;     // the partial sums of either
     size_t dct, partial, planes, colt, dw_gemm, dxt, dx_gemm;
-    size_t dw_phase() const { return one_pass || small ? partial : planes + colt + dw_gemm; }
+    size_t dw_phase() const { return one_pass || small || wide.ok ? partial : planes + colt + dw_gemm; }
     size_t dx_phase() const { return dxt + dx_gemm; }
 };
 
@@ -1150,6 +1647,8 @@ BwdLayout bwd_layout(const ConvGeom &g, const ConvDims &v, int in_dtype, bool al
     BwdLayout l{};
     l.one_pass = dw_one_pass(g, in_dtype, allow_split);
     l.small = !l.one_pass && small_dw(g);
+    l.wide = dw_wide(g, in_dtype, allow_split);
+    l.wide.ok = l.wide.ok && !l.one_pass && !l.small;
     l.dct = align_up((size_t)g.Co * v.ldm * sizeof(float));
     if (l.one_pass) {
         l.chunks = min(g.NB, kDwMaxGrid);
@@ -1157,14 +1656,19 @@ BwdLayout bwd_layout(const ConvGeom &g, const ConvDims &v, int in_dtype, bool al
     } else if (l.small) {
         l.chunks = small_dw_chunks(g, v.Q);
         l.partial = align_up((size_t)l.chunks * g.Co * v.Kc * sizeof(float));
+    } else if (l.wide.ok) {
+        l.chunks = l.wide.slices;
+        l.partial = align_up((size_t)l.chunks * g.Co * v.Kc * sizeof(float));
     } else {
         const GemmArgs w = dw_args(g, v, in_dtype, allow_split);
         l.planes = w.a_dtype == kPlanes3 ? align_up((size_t)3 * g.Co * v.ldm * sizeof(uint16_t)) : 0;
         l.colt = align_up((size_t)v.Kc * v.ldm * dtype_bytes(in_dtype));
         l.dw_gemm = gemm_ws(w);
     }
-    l.dxt = align_up((size_t)v.Kc * v.ldm * sizeof(float));
-    l.dx_gemm = gemm_ws(dx_args(g, v, allow_split));
+    if (!dx_wide(g, allow_split)) {
+        l.dxt = align_up((size_t)v.Kc * v.ldm * sizeof(float));
+        l.dx_gemm = gemm_ws(dx_args(g, v, allow_split));
+    }
     return l;
 }
 
@@ -1309,8 +1813,9 @@ hipError_t launch_conv_pool_bwd(const ConvGeom &g, const float *dI, const uint8_
     char *rest = base + l.dct;
     const size_t rest_bytes = ws_bytes - l.dct;
     hipError_t e;
-    const bool dx1 = grad_x && dx_one_pass(g, allow_split);
-    const bool dw_gemm = grad_w && !l.one_pass && !l.small;
+    const bool dxw = grad_x && dx_wide(g, allow_split);
+    const bool dx1 = grad_x && (dxw || dx_one_pass(g, allow_split));
+    const bool dw_gemm = grad_w && !l.one_pass && !l.small && !l.wide.ok;
     // dC^T in fp32 feeds the two-pass input gradient and an fp32 weight gradient
     const bool need_dct = (grad_x && !dx1) || (dw_gemm && l.planes == 0);
     if ((grad_x && !dx1) || dw_gemm) {
@@ -1337,6 +1842,16 @@ hipError_t launch_conv_pool_bwd(const ConvGeom &g, const float *dI, const uint8_
         if (e != hipSuccess) return e;
         e = launch_splitk_reduce(g.Co, v.Kc, l.chunks, partial, grad_w, v.Kc, nullptr, s);
         if (e != hipSuccess) return e;
+    } else if (grad_w && l.wide.ok) {
+        float *partial = reinterpret_cast<float *>(rest);
+        conv_dw_wide_kernel<<<(unsigned)(l.wide.groups * l.wide.cogroups * l.chunks), kDxThreads, 0,
+                              s>>>(g.NB, g.Ci, g.H, g.W, g.Co, g.Hp, g.Wp, l.wide.groups,
+                                   l.wide.cpg, l.wide.cogroups, dI, arg,
+                                   reinterpret_cast<const uint8_t *>(x), partial);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = launch_splitk_reduce(g.Co, v.Kc, l.chunks, partial, grad_w, v.Kc, nullptr, s);
+        if (e != hipSuccess) return e;
     } else if (grad_w) {
         char *colt = rest + l.planes;
         if (in_dtype == SNN_U8) launch_im2col_t<uint8_t>(g, v, x, colt, s);
@@ -1349,6 +1864,7 @@ hipError_t launch_conv_pool_bwd(const ConvGeom &g, const float *dI, const uint8_
         e = launch_gemm(a, colt + l.colt, rest_bytes - l.planes - l.colt, s);
         if (e != hipSuccess) return e;
     }
+    if (dxw) return launch_dx_wide(g, dI, arg, reinterpret_cast<const float *>(w), grad_x, s);
     if (dx1) {
         const unsigned grid = (unsigned)min(g.NB, device_cus());
         const int hw = g.H * g.W;  // at most 259 under dx_one_pass
