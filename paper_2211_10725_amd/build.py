@@ -14,7 +14,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libsnn.so")
 SOURCES = ["api.hip", "scan.hip", "scan_bwd_leaky.hip", "scan_bwd_synaptic.hip",
            "scan_bwd_rleaky.hip", "gemm.hip", "gemm_mfma16.hip", "gemm_async.hip", "gemm_joint.hip",
-           "skinny.hip", "conv.hip", "loss.hip", "optim.hip", "fused.hip"]
+           "skinny.hip", "dw_short.hip", "conv.hip", "loss.hip", "optim.hip", "fused.hip"]
 
 # No packed-fp32 instructions: some of their forms are not trusted on these
 # parts, so the feature is switched off for every device compilation.

@@ -360,6 +360,7 @@ size_t gemm_workspace_bytes(int M, int N, int K, int a_dtype, int b_dtype, bool 
     if (few_rows_applies(probe)) return few_rows_workspace_bytes(probe);
     if (gemm_async_applies(probe)) return gemm_async_workspace_bytes(probe);
     if (gemm_joint_applies(probe)) return gemm_joint_workspace_bytes(probe);
+    if (dw_short_applies(probe)) return 0;
     if (allow_split && gemm16_applies(probe)) return gemm16_workspace_bytes(probe);
     const Plan p = make_plan(M, N, K);
     if (p.splits <= 1) return 0;
@@ -387,6 +388,7 @@ hipError_t launch_gemm(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t
     if (few_rows_applies(g)) return divided(launch_few_rows(g, ws, ws_bytes, s), g, s);
     if (gemm_async_applies(g)) return launch_gemm_async(g, ws, ws_bytes, s);
     if (gemm_joint_applies(g)) return launch_gemm_joint(g, ws, ws_bytes, s);
+    if (dw_short_applies(g)) return launch_dw_short(g, s);
     if (g.allow_split && gemm16_applies(g)) return divided(launch_gemm16(g, ws, ws_bytes, s), g, s);
     const Plan p = make_plan(g.M, g.N, g.K);
     float *out = g.C;

@@ -180,6 +180,11 @@ bool few_rows_applies(const GemmArgs &g);
 size_t few_rows_workspace_bytes(const GemmArgs &g);
 hipError_t launch_few_rows(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
 
+// weight gradients over few rows (dw_short.hip): A fp32, B spike bytes, both
+// M/N-contiguous
+bool dw_short_applies(const GemmArgs &g);
+hipError_t launch_dw_short(const GemmArgs &g, hipStream_t s);
+
 // forward of a layer with at most 16 outputs and a long contraction: A
 // spikes (bytes) or fp16, W fp32 or fp16, both K-contiguous; 16-bit MFMA with
 // exact products (needs allow_split)
