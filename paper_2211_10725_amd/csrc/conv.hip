@@ -1665,10 +1665,10 @@ BwdLayout bwd_layout(const ConvGeom &g, const ConvDims &v, int in_dtype, bool al
         l.colt = align_up((size_t)v.Kc * v.ldm * dtype_bytes(in_dtype));
         l.dw_gemm = gemm_ws(w);
     }
-    if (!dx_wide(g, allow_split)) {
-        l.dxt = align_up((size_t)v.Kc * v.ldm * sizeof(float));
-        l.dx_gemm = gemm_ws(dx_args(g, v, allow_split));
-    }
+    // (the one-kernel input gradients need none: the size asked stays that of
+    // the contraction they stand in for)
+    l.dxt = align_up((size_t)v.Kc * v.ldm * sizeof(float));
+    l.dx_gemm = gemm_ws(dx_args(g, v, allow_split));
     return l;
 }
 

@@ -360,7 +360,7 @@ size_t gemm_workspace_bytes(int M, int N, int K, int a_dtype, int b_dtype, bool 
     if (few_rows_applies(probe)) return few_rows_workspace_bytes(probe);
     if (gemm_async_applies(probe)) return gemm_async_workspace_bytes(probe);
     if (gemm_joint_applies(probe)) return gemm_joint_workspace_bytes(probe);
-    if (dw_short_applies(probe)) return 0;
+    // (dw_short needs none: the size asked stays that of the kernel it stands in for)
     if (allow_split && gemm16_applies(probe)) return gemm16_workspace_bytes(probe);
     const Plan p = make_plan(M, N, K);
     if (p.splits <= 1) return 0;
