@@ -371,7 +371,7 @@ def main():
     params = wls.init_params(wl, args.seed)
     # a scan-only layer's spikes (read by nothing in the step) packed to bits;
     # an fp32 net's input spikes stored as bf16 0/1 when its first product
-    # runs on the asynchronous kernel's three-plane mode (no widening passes)
+    # takes the parts of fp32 weights in turn (no byte conversion)
     l0 = wl.layers[0]
     bf16_in = (wl.dtype == "f32" and l0["kind"] == "dense" and not args.fp32_mfma and
                _async_ok(3, 0, wl.T * wl.B, l0["n_out"], l0["n_in"]))
@@ -658,6 +658,8 @@ def _contraction_kind(net, li, fp32_mfma, stage="synapse_fwd"):
         if fp32_mfma:
             return "mfma32", 1
         a, b = d.grad_dtype, d.w_dtype
+        if a == 0 and b == 0 and _joint_ok(d.T * d.B, d.n_in, d.n_out):
+            return "mfma16", 6  # six of the nine part products
         p = _parts(a, b) * _parts(b, a)
         return ("mfma16", p) if p <= 6 else ("mfma32", 1)
     # conv backward: one-pass kernels on the 16-bit cores (dW 3 exact passes,
@@ -708,10 +710,9 @@ def _narrow_contraction(net, li, fp32_mfma):
 
 
 def _async_passes(a, b, M, N, K, mn=False):
-    """Mirrors gemm_async_applies in gemm_async.hip: 0 when the asynchronous
-    256x256 kernel does not take the product, else its MFMA passes (3 for
-    spikes against an fp32 operand held as three bf16 planes).  mn: both
-    operands M/N-contiguous."""
+    """0 where 256x256 tiles do not fill the device, else the MFMA passes (3
+    for spikes against an fp32 operand as three bf16 parts, which the joint
+    kernel runs).  mn: both operands M/N-contiguous."""
     if K % 8 or K < 256 or M < 256 or N < 256 or (mn and (M % 8 or N % 8)):
         return 0
     if (a, b) in ((0, 3), (3, 0), (0, 2), (2, 0)):  # fp32 against spikes or bf16
@@ -723,6 +724,11 @@ def _async_passes(a, b, M, N, K, mn=False):
         return 3 if tiles * splits >= 192 and M * N * K >= 2 ** 32 else 0
     ok_type = (a in (3, 1) and b in (3, 1)) or (a in (3, 2) and b in (3, 2))
     return 1 if ok_type and M * N * K >= 2 ** 30 else 0
+
+
+def _joint_ok(M, N, K):
+    """Mirrors gemm_joint_applies in gemm_joint.hip for fp32 operands."""
+    return M >= 64 and N >= 64 and K >= 192 and M * N * K >= 2 ** 30
 
 
 def _async_ok(a, b, M, N, K, mn=False):
@@ -757,6 +763,12 @@ def _stage_kernels(net, name, li, fp32_mfma):
                 return ": few_rows_mfma_kernel / few_rows_kernel + splitk_reduce_kernel"
             # mirrors dw_plan in api.hip
             sfx = f" ({passes} pass{'es' if passes > 1 else ''}, + splitk_reduce_kernel when split over K)"
+            if (not fp32_mfma and d.grad_dtype == 0 and d.in_dtype in (2, 3) and
+                    _joint_ok(d.n_out, d.n_in, M)):
+                return f": pack_kernel + gemm_joint_kernel{sfx}"
+            if (not fp32_mfma and d.grad_dtype == 0 and d.in_dtype == 3 and d.n_out >= 64 and
+                    d.n_in >= 64 and 64 <= M <= 1024):
+                return ": dw_short_kernel (3 passes)"
             if (not fp32_mfma and d.synapse == 0 and
                     _async_ok(d.grad_dtype, d.in_dtype, d.n_out, d.n_in, M, mn=True)):
                 what = ("dL/dI (the 3 bf16 planes the reverse scan writes)" if d.grad_dtype == 0
@@ -773,6 +785,9 @@ def _stage_kernels(net, name, li, fp32_mfma):
                                                   else "") + ") + transpose_u8_kernel (x^T) + "
                    if trans else "")
             return f": {pre}{gemm}{sfx}"
+        if not fp32_mfma and d.grad_dtype == 0 and d.w_dtype == 0 and _joint_ok(M, d.n_in, K):
+            return (": pack_kernel + gemm_joint_kernel (6 passes, + splitk_reduce_kernel when "
+                    "split over K)")
         big = 2.0 * M * d.n_in * K >= 2 ** 30
         gemm = ("gemm_async_kernel" if big and passes == 1 and
                 _async_ok(d.grad_dtype, d.w_dtype, M, d.n_in, K) else
@@ -799,9 +814,7 @@ def _stage_kernels(net, name, li, fp32_mfma):
                 "(conv weight and input gradients)")
     if name == "synapse_fwd" and _async_contraction(net, li, fp32_mfma):
         if d.w_dtype == 0:
-            widen = "widen_kernel (spikes to bf16) + " if d.in_dtype == 3 else ""
-            return (f": {widen}split_planes_kernel (weights as 3 bf16 planes) + "
-                    "gemm_async_kernel (3 passes)")
+            return ": pack_kernel (weights as 3 bf16 parts) + gemm_joint_kernel (3 passes)"
         widen = " widen_kernel (spikes to fp16) +" if d.in_dtype == 3 else ""
         return f":{widen} gemm_async_kernel"
     if name == "synapse_fwd" and _narrow_contraction(net, li, fp32_mfma):
