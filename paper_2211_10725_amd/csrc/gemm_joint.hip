@@ -22,10 +22,10 @@
 // copied once for three MFMAs per fragment, and every copy instruction should
 // touch whole 128-byte lines: operands that are rewritten anyway go in
 // fragment order, 1 KiB of consecutive memory per copy.  Measured, contraction
-// with its rewriting (start: the 16-bit kernel, the 256 x 256 kernel with its
+// with its rewriting (before: the 16-bit kernel, the 256 x 256 kernel with its
 // planes in turn, or fp32 MFMA):
-//    6400 x 1000 x 1000  fp32 forward 87 -> 53 us, dx 189 -> 122 us
-//    2013 x 1003 x 1101  fp32 forward 96 -> 39, dW 65 -> 41, dx 87 -> 53 us
+//    6400 x 1000 x 1000  fp32 forward 87 -> 66 us, dx 189 -> 111 us
+//    2013 x 1003 x 1101  fp32 forward 96 -> 34, dW 65 -> 41, dx 87 -> 53 us
 //    6400 x 1000 x 1000  fp16 forward 37 -> 26, dW 44 -> 32, dx 43 -> 27 us
 //    5000 x 1500 x  700  fp16 forward 118 -> 42, dW 64 -> 47, dx 121 -> 33 us
 //
@@ -778,7 +778,11 @@ struct Shape { int BM, BN, KT, R, per_cu; float step_us; };
 // parts the latter moves 5/8 of the bytes into LDS (53 against 55 us); for
 // three by three, 256 x 128 takes 122 against 126 us there, but 128 x 128
 // leaves a smaller last wave on narrow outputs (181 against 203 us on 12800 x
-// 784 x 1000).
+// 784 x 1000).  Currents: parts in turn, 256 x 256 tiles one chunk each (73 us
+// on 12800 x 1000 x 784, 200 tiles) or 256 x 128 ones that fold the chunks (56
+// us on 6400 x 1000 x 1000); parts within a step, 128 x 128 tiles where 256 x
+// 128 ones leave most compute units idle (25 against 37 us on 2013 x 1101 x
+// 1003, 144 and 72 tiles).
 constexpr Shape kShapes[] = {{0, 0, 0, 0, 0, 0.f},
                              {128, 128, 64, 2, 2, 1.4f},
                              {256, 128, 32, 3, 1, 1.3f},
