@@ -248,11 +248,12 @@ __global__ __launch_bounds__(kThreads) void grad_bound_kernel(int64_t rows, int 
                                                               const void *__restrict__ w,
                                                               float *__restrict__ partial) {
     __shared__ float red[kThreads / 64];
-    // rows of `width` values: the max over rows of sum |x| (width 1: max |x|,
-    // an fp32 gradient of every step read 64 bytes per lane at a time: 26 MB
-    // in 11.7 us one value at a time)
+    // rows of `width` values of type dt: the max over rows of sum |x| (fp32
+    // rows of one value, the gradient of every step or of a column, are read
+    // 64 bytes per lane at a time: 26 MB in 11.7 us one value at a time; a
+    // folded layer of one output may bring 16-bit ones)
     float m1 = 0.f;
-    if (width == 1) {
+    if (width == 1 && dt == SNN_F32) {
         const float4 *x4 = reinterpret_cast<const float4 *>(src);
         const int64_t n4 = rows / 4, step = (int64_t)gridDim.x * kThreads;
         int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;

@@ -297,6 +297,44 @@ def test_scan_bwd_fold_half_operands():
     assert_close(_np(gb), ref.sum(axis=(0, 1)), 1e-3, what="db (folded)")
 
 
+@pytest.mark.parametrize("updt", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("wdt", [torch.float32, torch.float16])
+@pytest.mark.parametrize("T,B,nup", [(7, 3, 1), (1, 1, 1), (33, 37, 1), (7, 3, 2)])
+def test_scan_bwd_fold_scale(updt, wdt, T, B, nup):
+    """The scale of an fp16 dL/dI below a folded layer of one output, whose
+    dL/dI may be fp32, bf16 or fp16 (an odd number of rows): the largest power
+    of two S with G F S <= 2^15, G and F from the given values.  The values
+    after the last row are large, so that reading one of them shows."""
+    N = 64
+    rng = np.random.default_rng(T + B + nup)
+    I = rng.normal(0.3, 0.8, (T, B, N)).astype(np.float32)
+    spec = dict(kind="dense", n_in=8, n_out=N, neuron="leaky", beta=0.9)
+    d = snn.layer_desc(spec, T, B, grad_dtype=snn.F16)
+    dn, _ = _none_desc(T, B, N, "leaky", 0.9)
+    spk = torch.empty((T, B, N), dtype=torch.uint8, device=DEV)
+    x, ck = _t(I), snn.ckpt_buffer(dn)
+    snn.snn_neuron_fwd(dn, x, None, spk, ck, None)
+    _, u, _ = oracle.scan_fwd(I, "leaky", 0.9, 1.0)
+    # magnitudes ascending along the rows, the largest at an even index
+    mag = rng.uniform(0.5, 1.0, (T, B, nup)) * np.linspace(0.01, 0.1, T * B).reshape(T, B, 1)
+    mag.reshape(-1, nup)[(T * B - 1) // 2 * 2] = 0.11
+    dup = torch.as_tensor(mag * rng.choice([-1.0, 1.0], mag.shape)).to(updt)
+    wup = torch.as_tensor(rng.uniform(-1, 1, (nup, N))).to(wdt)
+    buf = torch.full((4 * T * B * nup + 64,), 1e4, dtype=updt, device=DEV)
+    buf[:dup.numel()] = dup.flatten().to(DEV)
+    dI = torch.empty((T, B, N), dtype=torch.float16, device=DEV)
+    sc = torch.full((4,), float("nan"), device=DEV)
+    snn.snn_neuron_bwd(d, snn.GRAD_FOLD, (buf[:dup.numel()].view(T, B, nup), wup.to(DEV)), None, x,
+                       ck, dI, None, None, _ws(snn.snn_layer_workspace_bytes(d)), dcur_scale=sc)
+    du, wu = dup.double().numpy(), wup.double().numpy()
+    F = (1.0 - 0.9 ** T) / (1.0 - 0.9)
+    S = float(_np(sc)[0])
+    # (one row's sum is exact or, of two values, rounded once: no power of two is near)
+    assert S == pow2_scale([np.abs(du).sum(-1).max() * np.abs(wu).max() * F])
+    ref = oracle.scan_bwd(u, du @ wu, "leaky", 0.9, 1.0, 25.0)
+    assert_close(_np(dI.float()) / S, ref, 2e-2, what="fp16 dL/dI (folded)")
+
+
 def _bf16_parts(x):
     """The three exact bf16 parts of fp32 values, hi = bf16(x), mid =
     bf16(x - hi), lo = bf16(x - hi - mid) (round to nearest even; every
