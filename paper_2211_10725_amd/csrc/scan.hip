@@ -443,7 +443,7 @@ hipError_t launch_grad_scale(int T, int64_t C, const BwdGrad &grad, int B, doubl
         width = grad.nup;
         dt = grad.dt_up;
         src = grad.dup;
-        nw = (int64_t)grad.nup * (C / B);
+        nw = B > 0 ? (int64_t)grad.nup * (C / B) : 0;  // (an empty batch: no bound)
         w = grad.wup;
         dt_w = grad.dt_w;
     } else {

@@ -335,6 +335,18 @@ def test_scan_bwd_fold_scale(updt, wdt, T, B, nup):
     assert_close(_np(dI.float()) / S, ref, 2e-2, what="fp16 dL/dI (folded)")
 
 
+def test_scan_bwd_fold_scale_of_an_empty_batch():
+    """No samples: the scale of the empty gradient is 1."""
+    d = snn.layer_desc(dict(kind="dense", n_in=8, n_out=64, neuron="leaky", beta=0.9), 5, 0,
+                       grad_dtype=snn.F16)
+    sc = torch.full((4,), float("nan"), device=DEV)
+    buf = torch.zeros(64, device=DEV)
+    snn.snn_neuron_bwd(d, snn.GRAD_FOLD, (buf, torch.ones((10, 64), device=DEV)), None, buf, None,
+                       torch.empty(64, dtype=torch.float16, device=DEV), None, None,
+                       _ws(snn.snn_layer_workspace_bytes(d)), dcur_scale=sc)
+    assert float(_np(sc)[0]) == 1.0
+
+
 def _bf16_parts(x):
     """The three exact bf16 parts of fp32 values, hi = bf16(x), mid =
     bf16(x - hi), lo = bf16(x - hi - mid) (round to nearest even; every
