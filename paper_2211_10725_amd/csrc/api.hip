@@ -557,11 +557,12 @@ snn_status synapse_bwd(const snn_layer_desc *d, const void *dcur, const void *dc
                        const float *dcur_scale, const uint8_t *pool_arg, const void *x,
                        const void *w, float *grad_w, float *grad_x, void *ws,
                        size_t ws_bytes, hipStream_t stream) {
-    // dcur_t (the transposed weight-gradient operand) serves the weight
-    // gradient when the layer's plan contracts it; dcur everything else
+    // dcur_t (the weight gradient's operand) serves the weight gradient when
+    // the layer's plan contracts it, and the input gradient only without a
+    // dcur (the layer call); dcur everything else
     const bool use_t = dcur_t && grad_w && dcur_t_bytes(d) > 0;
     if (dcur_t && !aligned16(dcur_t)) return SNN_ERR_ALIGN;
-    const bool dx_t = dcur_t && grad_x && dx_from_planes(d);
+    const bool dx_t = !dcur && dcur_t && grad_x && dx_from_planes(d);
     if (!dcur && ((grad_x && !dx_t) || (grad_w && !use_t))) return SNN_ERR_NULL;
     if (!dcur && !dcur_t) return SNN_ERR_NULL;
     if (scaled_grad(d)) {

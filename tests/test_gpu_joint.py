@@ -117,6 +117,33 @@ def test_input_gradient_of_special_values(bad, from_planes):
     assert bool(((gx.double() - ref.double()).abs()[fin] <= tol[fin]).all())
 
 
+@pytest.mark.parametrize("M", [64, 1600])
+def test_input_gradient_follows_dcur(M):
+    """Of the stage call's two forms of dL/dI the weight gradient contracts
+    dcur_t where the layer has such an operand, and the input gradient dcur,
+    whatever the size: a caller may have masked it in between."""
+    n_in, n_out = 768, 1000
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, 9)
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    saved = torch.zeros(snn.snn_layer_saved_bytes(d), dtype=torch.uint8, device="cuda")
+    dcur = torch.empty((M, n_out), device="cuda")
+    dt = torch.empty(max(snn.snn_layer_dcur_t_bytes(d), 6 * M * n_out), dtype=torch.uint8,
+                     device="cuda")
+    cur, ck, _ = snn.saved_parts(d, saved)
+    snn.snn_neuron_bwd(d, snn.GRAD_FULL, dI, None, cur, ck, dcur, None, None, ws, dcur_t=dt)
+    masked = dcur * (torch.arange(n_out, device="cuda") % 3 == 0)
+    out = []
+    for t, both in ((dt, True), (None, True), (dt, False)):
+        gW, gx = torch.empty_like(W), torch.empty((M, n_in), device="cuda")
+        snn.snn_synapse_bwd(d, masked, None, x, W, gW if both else None, gx, ws, dcur_t=t)
+        out.append((gW, gx))
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[2][1], out[1][1])
+    ref = masked.double() @ W.double()
+    _within(out[0][1], ref, masked.double().abs() @ W.double().abs(), 6 * n_out, 2.0 ** -26, "dx")
+    rw = (dcur if snn.snn_layer_dcur_t_bytes(d) else masked).double()
+    _within(out[0][0], rw.t() @ x.double(), rw.abs().t() @ x.double(), 3 * M, 0.0, "dW")
+
+
 # parts in turn: one 256 x 256 item per tile; chunks of K folded by a workgroup;
 # one wave of 128 x 128 tiles against 256 x 128 ones, with one chunk and several
 @pytest.mark.parametrize("M,n_in,n_out", [(12801, 784, 1000), (6401, 1000, 1001), (2013, 1003, 1101),
