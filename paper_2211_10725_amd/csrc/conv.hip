@@ -1629,7 +1629,12 @@ GemmArgs dx_args(const ConvGeom &g, const ConvDims &v, bool allow_split) {
     return a;
 }
 
+// dC^T as planes against col^T: always the 16-bit kernel.  Its smaller tiles
+// beat 256 x 256 ones with the planes in turn on these few, deep tiles (dW of
+// 256 images of 64 x 24 x 24 to 256 channels 413 against 514 us, 1024 of 24 x
+// 18 x 18 to 256 372 against 494, 224 of 12 x 20 x 20 to 256 91 either way).
 size_t gemm_ws(const GemmArgs &a) {
+    if (a.a_dtype == kPlanes3) return gemm16_workspace_bytes(a);
     return gemm_workspace_bytes(a.M, a.N, a.K, a.a_dtype, a.b_dtype, a.a_kc, a.b_kc, a.allow_split);
 }
 
@@ -1861,7 +1866,10 @@ hipError_t launch_conv_pool_bwd(const ConvGeom &g, const float *dI, const uint8_
         GemmArgs a = dw_args(g, v, in_dtype, allow_split);
         a.A = a.a_dtype == kPlanes3 ? static_cast<const void *>(rest) : dct;
         a.B = colt; a.C = grad_w; a.bias = nullptr;
-        e = launch_gemm(a, colt + l.colt, rest_bytes - l.planes - l.colt, s);
+        char *gws = colt + l.colt;
+        const size_t gws_bytes = rest_bytes - l.planes - l.colt;
+        e = a.a_dtype == kPlanes3 ? launch_gemm16(a, gws, gws_bytes, s)
+                                  : launch_gemm(a, gws, gws_bytes, s);
         if (e != hipSuccess) return e;
     }
     if (dxw) return launch_dx_wide(g, dI, arg, reinterpret_cast<const float *>(w), grad_x, s);

@@ -162,3 +162,81 @@ def test_currents_in_the_kept_order(M, n_in, n_out, bytes_in):
     xd, Wd = x.double(), W.double()
     _within(cur, xd @ Wd.t() + b.double(), xd @ Wd.abs().t() + b.double().abs(), 3 * n_in + 1, 0.0,
             "currents")
+
+
+# Products of spikes with three parts that the joint kernel leaves to 256 x 256
+# tiles with the parts in turn.
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(9000, 1024, 1001), (8200, 1288, 515), (65544, 264, 270)])
+def test_weight_gradient_of_parts_in_turn(M, n_in, n_out):
+    """K-contiguous planes: more than 8192 rows, outputs no multiple of 8.  A
+    column of x with one spike gives the row of dL/dI there, bit for bit; one
+    with many, their sum within the fp32 bound."""
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, n_out)
+    hot = torch.randint(0, M, (n_in,), device="cuda")
+    some = torch.arange(n_in, device="cuda") % 3 != 0
+    x[:, some] = 0
+    x[hot[some], some.nonzero().flatten()] = 1
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    gW = torch.full((n_out, n_in), float("nan"), device="cuda")
+    snn.snn_synapse_bwd(d, dI, None, x, W, gW, None, ws)
+    assert torch.equal(gW[:, some], dI[hot[some]].t())
+    xd, dd = x.double(), dI.double()
+    _within(gW, dd.t() @ xd, dd.abs().t() @ xd, 3 * M, 0.0, "dW")
+
+
+def test_conv_weight_gradient_of_planes():
+    """256 output channels, 64 pooled cells.  Each output channel has its
+    gradient in one cell, so its dW is that value where the spikes are, bit for
+    bit."""
+    NB, Ci, H, Co = 224, 12, 20, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    d = snn.layer_desc(dict(kind="conv", c_in=Ci, h=H, w=H, c_out=Co, neuron="leaky", beta=0.5), 1, NB)
+    x = (torch.rand((NB, Ci, H, H), generator=g, device="cuda") < 0.4).to(torch.uint8)
+    w = torch.rand((Co, Ci, 5, 5), generator=g, device="cuda")
+    arg = torch.randint(0, 4, (NB, Co, 8, 8), generator=g, device="cuda", dtype=torch.uint8)
+    dI = torch.zeros((NB, Co, 8, 8), device="cuda")
+    nb = torch.randint(0, NB, (Co,), generator=g, device="cuda")
+    q = torch.randint(0, 64, (Co,), generator=g, device="cuda")
+    co = torch.arange(Co, device="cuda")
+    v = torch.randn(Co, generator=g, device="cuda")
+    dI.view(NB, Co, 64)[nb, co, q] = v
+    a = arg.view(NB, Co, 64)[nb, co, q].long()
+    oy, ox = 2 * (q // 8) + a // 2, 2 * (q % 8) + a % 2
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    gW = torch.full_like(w, float("nan"))
+    snn.snn_synapse_bwd(d, dI, arg, x, w, gW, None, ws)
+    ref = torch.stack([x[nb[c], :, oy[c]:oy[c] + 5, ox[c]:ox[c] + 5].float() * v[c] for c in range(Co)])
+    assert torch.equal(gW, ref)
+
+
+def test_operands_past_two_to_the_31():
+    """Spikes of more than 2^31 elements: the currents of the last rows are bit
+    for bit those of a call with these rows alone (one chunk of K in both), and
+    the weight gradient of small whole numbers is exact."""
+    n_in, n_out, M, tail = 8192, 256, (1 << 18) + 520, 1 << 17
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    x = torch.randint(0, 2, (M, n_in), generator=g, device="cuda", dtype=torch.uint8)
+    W = torch.rand((n_out, n_in), generator=g, device="cuda") * 2 - 1
+    b = torch.rand(n_out, generator=g, device="cuda")
+    spec = dict(kind="dense", n_in=n_in, n_out=n_out, neuron="leaky", beta=0.9)
+    out = []
+    for rows in (M, tail):
+        d = snn.layer_desc(spec, 1, rows)
+        ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+        cur = torch.full((rows, n_out), float("nan"), device="cuda")
+        snn.snn_synapse_fwd(d, x[M - rows:], W, b, cur, None, ws)
+        out.append(cur[rows - tail:])
+    assert torch.equal(out[0], out[1])
+    d = snn.layer_desc(spec, 1, M)
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    dI = torch.randint(-3, 4, (M, n_out), generator=g, device="cuda").float()
+    gW = torch.full((n_out, n_in), float("nan"), device="cuda")
+    snn.snn_synapse_bwd(d, dI, None, x, W, gW, None, ws)
+    ref = torch.zeros((n_out, n_in), device="cuda")
+    for r in range(0, M, 1 << 15):  # sums of whole numbers below 2^24
+        ref += dI[r:r + (1 << 15)].t() @ x[r:r + (1 << 15)].float()
+    assert torch.equal(gW, ref)
