@@ -1487,7 +1487,7 @@ __global__ __launch_bounds__(kThreads) void conv_dw_small_kernel(
 int small_dw_chunks(const ConvGeom &g, int64_t Q) {
     const int64_t by_cells = (Q + kThreads - 1) / kThreads;
     const int64_t by_grid = max(1, 1024 / g.Co);
-    return (int)max((int64_t)1, min(by_cells, by_grid));
+    return (int)std::max<int64_t>(1, std::min(by_cells, by_grid));
 }
 
 bool small_dw(const ConvGeom &g) { return g.Ci * KS * KS <= 75; }
@@ -1738,7 +1738,7 @@ size_t conv_bwd_workspace_bytes(const ConvGeom &g, int in_dtype, bool allow_spli
     const ConvDims v = dims_of(g);
     if (v.Mw == 0) return 0;
     const BwdLayout l = bwd_layout(g, v, in_dtype, allow_split);
-    return l.dct + max(l.dw_phase(), l.dx_phase());
+    return l.dct + larger(l.dw_phase(), l.dx_phase());
 }
 
 hipError_t launch_conv_pool_fwd(const ConvGeom &g, const void *x, int in_dtype, const void *w,

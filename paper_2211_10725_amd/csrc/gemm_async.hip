@@ -679,7 +679,7 @@ size_t gemm_async_workspace_bytes(const GemmArgs &g) {
     const size_t own = p.a_bytes + p.b_bytes + p.part_bytes;
     // asked without a bias, which takes layers this wide to the other kernels
     if (!g.bias && g.a_kc && g.N > kBiasLds)
-        return max(own, max(gemm_joint_workspace_bytes(g), gemm16_workspace_bytes(g)));
+        return larger(own, larger(gemm_joint_workspace_bytes(g), gemm16_workspace_bytes(g)));
     return own;
 }
 

@@ -955,7 +955,7 @@ size_t gemm_order_part_bytes(const GemmArgs &g) {
     const size_t turn = chunk > 0 && chunk < g.K
                             ? align_up((size_t)((g.K + chunk - 1) / chunk) * g.M * g.N * sizeof(float))
                             : 0;
-    return max(turn, gemm16_workspace_bytes(o));
+    return larger(turn, gemm16_workspace_bytes(o));
 }
 }  // namespace
 
@@ -964,7 +964,7 @@ size_t gemm_joint_workspace_bytes(const GemmArgs &g) {
     const JointPlan p = make_plan(g);
     size_t part = p.part_bytes;
     // the chunks may depend on the device and on a bias: any plan's partials
-    if (g.a_kc && g.b_kc) part = max(part, gemm_order_part_bytes(g));
+    if (g.a_kc && g.b_kc) part = larger(part, gemm_order_part_bytes(g));
     return p.a.bytes + p.b.bytes + part;
 }
 

@@ -874,7 +874,7 @@ size_t gemm16_workspace_bytes(const GemmArgs &g) {
         p.tiles_m = (g.M + p.BM - 1) / p.BM;
         p.tiles_n = (g.N + p.BN - 1) / p.BN;
         finish_plan(p, g.M, g.N, g.K, kd, g.a_kc, g.b_kc, max_splits(p.tiles_m * p.tiles_n, ksteps, (int64_t)g.M * g.N));
-        best = max(best, p.plane_bytes + p.part_bytes);
+        best = larger(best, p.plane_bytes + p.part_bytes);
     }
     return best;
 }

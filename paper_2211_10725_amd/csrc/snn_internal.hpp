@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "snn.h"
 
 namespace snn {
@@ -29,6 +31,9 @@ __device__ inline int xcd_local_item() {
 // Internal operand type: an fp32 array held exactly as three bf16 planes
 // (hi, mid, lo), the plane stride given by GemmArgs::a_ps / b_ps.
 constexpr int kPlanes3 = 64;
+
+// the larger of two sizes (a plain max() of the HIP headers takes int on the host)
+inline size_t larger(size_t a, size_t b) { return std::max(a, b); }
 
 inline size_t dtype_bytes(int dt) {
     switch (dt) {

@@ -148,6 +148,24 @@ def _al(x):
     return (x + 255) // 256 * 256
 
 
+def test_workspace_of_large_layers():
+    """Workspaces of 2 GiB and more hold what the layer's calls put there."""
+    # a convolution: dL/dI, dC^T fp32 and dx^T fp32 of every window row
+    NB, Ci, hw, Co = 300, 32, 60, 300
+    d = snn.layer_desc(dict(kind="conv", c_in=Ci, h=hw, w=hw, c_out=Co, neuron="leaky", beta=0.5),
+                       1, NB)
+    windows = NB * (hw - 4) ** 2
+    assert snn.snn_layer_workspace_bytes(d) >= 4 * (NB * d.n_out + Co * windows + 25 * Ci * windows)
+    # fp16 weights, more outputs than a bias is staged for: bytes widened to fp16
+    for rows in (1 << 17, 1 << 18, 1 << 19):
+        d = snn.layer_desc(dict(kind="dense", n_in=8192, n_out=9000, neuron="leaky", beta=0.9), 1,
+                           rows, w_dtype=snn.F16, grad_dtype=snn.F16)
+        assert snn.snn_layer_workspace_bytes(d) >= 2 * rows * (8192 + 9000)
+    # fp32 weights of 3 planes of more than 2 GiB
+    d = snn.layer_desc(dict(kind="dense", n_in=184, n_out=2000000, neuron="leaky", beta=0.9), 1, 2048)
+    assert snn.snn_layer_workspace_bytes(d) >= 6 * 184 * 2000000
+
+
 @pytest.mark.parametrize("kind,neuron,T,B", [("dense", "leaky", 25, 32), ("dense", "synaptic", 50, 7),
                                              ("dense", "rleaky", 16, 3), ("dense", "leaky", 17, 3),
                                              ("dense", "leaky", 1, 5), ("conv", "leaky", 25, 4),
