@@ -342,6 +342,32 @@ void launch_btype(const GemmArgs &g, const Plan &p, float *out, int64_t ldo, int
 
 }  // namespace
 
+namespace {
+// of the 16-bit or the fp32 kernel (dw_short needs none: the size asked stays
+// that of the kernel it stands in for)
+size_t other_workspace_bytes(const GemmArgs &g) {
+    if (g.allow_split && gemm16_applies(g)) return gemm16_workspace_bytes(g);
+    const Plan p = make_plan(g.M, g.N, g.K);
+    if (p.splits <= 1) return 0;
+    return align_up((size_t)p.splits * g.M * g.N * sizeof(float));
+}
+}  // namespace
+
+// Fits to the times of 401 products (M of 64 .. 400000, N of 64 .. 16384, K of
+// 192 .. 16384; operand rows of whole 16 bytes or not), nine in ten within 15 %.
+double gemm_f32_us(int M, int N, int K) {
+    const Plan p = make_plan(M, N, K);
+    const double tile = (double)p.BM * p.BN * p.k_chunk / 1e6;
+    const double all = tile * p.tiles_m * p.tiles_n * p.splits / 1e3;
+    const double mb = (double)M * N * 4.0 * (p.splits > 1 ? 2 * p.splits + 2 : 1) / 1e6;
+    const bool small = p.BM * p.BN <= 64 * 64;
+    if (N % 4 == 0 && K % 4 == 0)
+        return small ? -0.6 + 15.2 * all + 8.7 * tile + 0.69 * mb
+                     : 9.3 + 15.1 * all + 5.2 * tile + 0.14 * mb;
+    return small ? -2.0 + 19.4 * all + 11.3 * tile + 0.88 * mb
+                 : 13.3 + 22.2 * all + 3.7 * tile + 0.16 * mb;
+}
+
 size_t gemm_workspace_bytes(int M, int N, int K, int a_dtype, int b_dtype, bool a_kc, bool b_kc,
                             bool allow_split) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
@@ -359,12 +385,11 @@ size_t gemm_workspace_bytes(int M, int N, int K, int a_dtype, int b_dtype, bool 
     if (short_k_applies(probe) || narrow_fwd_applies(probe)) return 0;
     if (few_rows_applies(probe)) return few_rows_workspace_bytes(probe);
     if (gemm_async_applies(probe)) return gemm_async_workspace_bytes(probe);
-    if (gemm_joint_applies(probe)) return gemm_joint_workspace_bytes(probe);
-    // (dw_short needs none: the size asked stays that of the kernel it stands in for)
-    if (allow_split && gemm16_applies(probe)) return gemm16_workspace_bytes(probe);
-    const Plan p = make_plan(M, N, K);
-    if (p.splits <= 1) return 0;
-    return align_up((size_t)p.splits * M * N * sizeof(float));
+    // (either's where the joint kernel fits: a bias, not given here, may change
+    // the order of summation and with it the choice)
+    if (gemm_joint_fits(probe))
+        return larger(gemm_joint_workspace_bytes(probe), other_workspace_bytes(probe));
+    return other_workspace_bytes(probe);
 }
 
 namespace {

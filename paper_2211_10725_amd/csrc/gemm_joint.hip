@@ -920,7 +920,7 @@ void launch_one(const GemmArgs &g, const JointArgs &a, hipStream_t s) {
 
 }  // namespace
 
-bool gemm_joint_applies(const GemmArgs &g) {
+bool gemm_joint_fits(const GemmArgs &g) {
     if (!g.allow_split || g.pool_hw > 0 || g.M < 64 || g.N < 64 || g.K < 192) return false;
     if (pair_type(g.a_dtype, g.b_dtype) < 0) return false;
     if (!g.a_kc && g.b_kc) return false;
@@ -943,6 +943,69 @@ bool gemm_joint_applies(const GemmArgs &g) {
     return (double)g.M * g.N * g.K >= 1073741824.0;
 }
 
+namespace {
+// The kernel with its rewriting against the kernels that run a product without
+// it, both from fits to measured times (1090 products of 64 .. 400000 rows and
+// 64 .. 16384 inputs and outputs, three classes: currents, dW, dx; this one
+// nine in ten within 12 %).  Tiles half empty, few rows or narrow layers and
+// deep splits go to the others: us, other kernel / this one,
+//   fp32 currents   64 rows 8192 -> 2048  30 / 59,  10715 rows 5776 -> 96  78 / 111
+//                   (6400 rows 1000 -> 1000  87 / 53,  2013 rows 1003 -> 1101  96 / 39)
+//   fp32 dW         262144 rows 64 -> 64  78 / 293,  4096 rows 64 -> 4096  29 / 59
+//                   (2013 rows 1003 -> 1101  65 / 41,  3000 rows 600 -> 600  42 / 31)
+//   fp32 dx         64 rows 8192 <- 2048  38 / 59,  16384 rows 64 <- 1024  50 / 62
+//                   (6400 rows 1000 <- 1000  189 / 122)
+// Choosing so loses 0.5 % against the better one on average.
+bool faster(const GemmArgs &g) {
+    GemmArgs o = g;
+    // (planes as the fp32 values they stand for: one choice for both)
+    if (o.a_dtype == kPlanes3) o.a_dtype = SNN_F32;
+    const bool dw = !o.a_kc && !o.b_kc;
+    const bool one = !fp32ish(o.a_dtype) && !fp32ish(o.b_dtype);
+    const bool nine = o.a_dtype == SNN_F32 && o.b_dtype == SNN_F32;
+    if (one && !dw) return true;
+    // bf16 spikes against fp32 go to the fp32 matrix cores otherwise
+    if (!one && !nine && o.a_dtype != SNN_U8 && o.b_dtype != SNN_U8) return true;
+    const JointPlan p = make_plan(o);
+    if (p.cfg == kTurnBig || p.cfg == kTurn) return true;
+    const Shape &sh = kShapes[p.cfg];
+    if (dw && (one || g.K > 8192)) {
+        // whole tiles' worth of work in flight
+        const double items = (double)p.splits * g.M * g.N / (sh.BM * sh.BN);
+        // 16-bit pairs: only the smallest outputs over the longest K are slower
+        // (64 x 64 over 262144 rows 53 / 115 us, 100 x 100 over 200000 71 / 69)
+        if (one) return items >= 18.0;
+        // More than 8192 rows are transposed for the other kernels: always
+        // slower where the rows are no whole 8 (96 x 5776 over 10715 464 / 86
+        // us), from 20 items where no whole 16 (120 x 264 over 61976 118 / 92; 96 x
+        // 200 over 365000 470 / 523), else from 50 (88 x 792 over 15504 55 / 45;
+        // 256 x 64 over 65536 64 / 101) of tiles more than half full (64 x 1024
+        // over 16384 42 / 45)
+        if (g.K % 16 != 0) return g.K % 8 != 0 || items >= 20.0;
+        return items >= 50.0 && 2 * g.M > p.tiles_m * sh.BM;
+    }
+    if (o.a_kc && o.b_kc) {
+        // currents: rewriting the weights for fewer than 100 rows costs more
+        // than it saves (80 rows 9420 <- 4722 133 / 201 us); with both sides long
+        // the 16-bit kernel's many tiles leave its estimate (4129 rows 192 ->
+        // 2584 49 / 33 us, 3968 of 592 -> 2544 70 / 55)
+        if (g.M < 100) return false;
+        if (g.M >= 2048 && g.N >= 2048) return true;
+    }
+    const double step = p.cfg == kThree ? 0.97 : p.cfg == kThreeSmall ? 0.56 : p.cfg == kThreeT ? 1.07
+                        : p.cfg == kNineBig ? 2.5 : 1.34;
+    const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * p.splits + 255) / 256;
+    const int steps = ((p.splits > 1 ? p.k_chunk : g.K) + sh.KT - 1) / sh.KT;
+    const double mb = (double)g.M * g.N * 4.0 * (p.splits > 1 ? 2 * p.splits + 2 : 1) / 1e6;
+    auto packed = [](int t, double n) { return n * (t == SNN_F32 ? 10.0 : 3.0) / 1e6; };
+    const double us = 13.0 + rounds * steps * step + 0.17 * mb +
+                      0.165 * (packed(o.a_dtype, (double)g.M * g.K) + packed(o.b_dtype, (double)g.N * g.K));
+    return us < (nine ? gemm_f32_us(g.M, g.N, g.K) : gemm16_us(o));
+}
+}  // namespace
+
+bool gemm_joint_applies(const GemmArgs &g) { return gemm_joint_fits(g) && faster(g); }
+
 double gemm_joint_us(const GemmArgs &g) {
     return gemm_joint_applies(g) ? make_plan(g).us : 1e300;
 }
@@ -960,7 +1023,7 @@ size_t gemm_order_part_bytes(const GemmArgs &g) {
 }  // namespace
 
 size_t gemm_joint_workspace_bytes(const GemmArgs &g) {
-    if (!gemm_joint_applies(g)) return 0;
+    if (!gemm_joint_fits(g)) return 0;
     const JointPlan p = make_plan(g);
     size_t part = p.part_bytes;
     // the chunks may depend on the device and on a bias: any plan's partials

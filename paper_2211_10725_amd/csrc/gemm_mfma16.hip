@@ -583,6 +583,7 @@ constexpr int kMaxSlotsPerCu = 8;  // upper bound on resident 256-thread blocks
 
 struct Plan16 {
     int shape, BM, BN, tiles_m, tiles_n, splits, k_chunk;
+    int64_t rounds;      // workgroups over those the device holds at once
     bool presplit;       // split the fp32 operand into bf16 planes once, up front
     size_t plane_bytes;  // workspace for those planes
     size_t part_bytes;   // workspace for split-K partial sums
@@ -714,6 +715,7 @@ Plan16 plan_for(const GemmArgs &g, const Kind &kd) {
         if (cost < best_cost) {
             best_cost = cost;
             best = p;
+            best.rounds = rounds;
         }
     }
     return best;
@@ -889,6 +891,32 @@ int gemm16_sum_chunk(const GemmArgs &g) {
     if (kd.mt == MT_F16 && kd.sa == SRC_H16 && kd.sb == SRC_H16)
         return plan_for<MT_F16, SRC_H16, true, SRC_H16, true>(g, kd).k_chunk;
     return 0;
+}
+
+// Fits to the times of 689 products of 64 .. 200000 rows and 64 .. 16384 inputs
+// and outputs of 2^30 .. 2^33 multiply-adds, nine in ten within 20 %.  What
+// separates the classes is the spike bytes' row length: rows of whole 16 bytes
+// are staged in 16-byte loads, of whole 8 or 4 in shorter ones, others byte by
+// byte.
+double gemm16_us(const GemmArgs &g) {
+    Plan16 p;
+    // us: constant, per 2^20 units of tile work (10^6), per MB of C and
+    // partials, for the reduction's launch
+    double c[4];
+    if (g.a_dtype == SNN_U8 && g.b_dtype == SNN_F32 && g.a_kc && g.b_kc) {
+        p = plan_for<MT_BF16, SRC_SPIKE, true, SRC_F32, true>(g, classify(SNN_U8, SNN_F32));
+        constexpr double t[3][4] = {{5.2, 4.93, 0.19, 5.0}, {-5.2, 12.5, 0.21, 12.4}, {-0.6, 17.7, 0.25, 8.4}};
+        for (int i = 0; i < 4; ++i) c[i] = t[g.lda % 16 == 0 ? 0 : g.lda % 8 == 0 ? 1 : 2][i];
+    } else if (g.a_dtype == SNN_F32 && g.b_dtype == SNN_U8 && !g.a_kc && !g.b_kc) {
+        p = plan_for<MT_BF16, SRC_F32, false, SRC_SPIKE, false>(g, classify(SNN_F32, SNN_U8));
+        constexpr double t[3][4] = {{10.2, 4.22, 0.15, 5.1}, {9.6, 6.35, 0.24, 1.5}, {10.4, 8.34, 0.2, 1.7}};
+        for (int i = 0; i < 4; ++i) c[i] = t[g.ldb % 16 == 0 ? 0 : g.ldb % 4 == 0 ? 1 : 2][i];
+    } else {
+        return 1e300;
+    }
+    const double work = (double)p.rounds * p.BM * p.BN * p.k_chunk * kShapeCost[0][p.shape] / 1e6;
+    const double mb = (double)g.M * g.N * 4.0 * (p.splits > 1 ? 2 * p.splits + 2 : 1) / 1e6;
+    return c[0] + c[1] * work + c[2] * mb + (p.splits > 1 ? c[3] : 0.0);
 }
 
 hipError_t launch_gemm16(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s) {

@@ -163,6 +163,9 @@ hipError_t launch_gemm(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t
 hipError_t launch_splitk_reduce(int M, int N, int S, const float *P, float *C, int64_t ldc,
                                 const float *bias, hipStream_t s, const float *c_div = nullptr);
 // C[m,n] /= c_div[0] for m < M, n < N
+// estimated time of an fp32 product A(m,k) B(k,n), A K-contiguous and B
+// N-contiguous, on the fp32 matrix cores
+double gemm_f32_us(int M, int N, int K);
 hipError_t launch_divide(int M, int N, float *C, int64_t ldc, const float *c_div, hipStream_t s);
 
 // ---- 16-bit matrix cores, exact products (gemm_mfma16.hip) ---------------------
@@ -171,6 +174,9 @@ size_t gemm16_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm16(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
 // length of the chunks of K that its plan sums one by one (0: not applicable)
 int gemm16_sum_chunk(const GemmArgs &g);
+// estimated time of a product of spike bytes and an fp32 operand, both
+// K-contiguous or both M/N-contiguous (1e300: another product)
+double gemm16_us(const GemmArgs &g);
 int gemm16_passes(const GemmArgs &g);  // MFMA passes per product, 0 if not applicable
 // dst[p][rows][ldp] = part p (hi, mid, lo) of the exact three-bf16 split of
 // src[r * ld + k], k < K; columns K .. ldp - 1 are 0
@@ -205,7 +211,8 @@ size_t gemm_async_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm_async(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);
 
 // ---- contractions whose operand parts are staged together (gemm_joint.hip) -----
-bool gemm_joint_applies(const GemmArgs &g);
+bool gemm_joint_fits(const GemmArgs &g);     // sizes and layouts that it can take
+bool gemm_joint_applies(const GemmArgs &g);  // ... and takes: where it is the faster one
 double gemm_joint_us(const GemmArgs &g);  // estimated time, 1e300 if not applicable
 size_t gemm_joint_workspace_bytes(const GemmArgs &g);
 hipError_t launch_gemm_joint(const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t s);

@@ -148,6 +148,21 @@ def _al(x):
     return (x + 255) // 256 * 256
 
 
+def test_narrow_weight_gradients_keep_their_kernel():
+    """The layout of dL/dI that a weight gradient contracts tells the kernel:
+    planes where the parts are staged together.  Outputs of a tile or two over
+    very many rows are slower there and keep the transposed operand."""
+    for rows, n_in, n_out, planes in [(262144, 64, 64, False), (65536, 256, 64, False),
+                                      (189920, 120, 72, False), (16384, 1024, 64, False),
+                                      (10715, 5776, 96, True), (61976, 264, 120, True),
+                                      (15504, 792, 88, True), (12800, 1000, 1000, True)]:
+        d = snn.layer_desc(dict(kind="dense", n_in=n_in, n_out=n_out, neuron="leaky", beta=0.9), 1,
+                           rows)
+        got = snn.snn_layer_dcur_t_layout(d) == snn.DCUR_T_PLANES
+        assert got == planes, (rows, n_in, n_out)
+        assert snn.snn_layer_dcur_t_bytes(d) >= 6 * rows * n_out
+
+
 def test_workspace_of_large_layers():
     """Workspaces of 2 GiB and more hold what the layer's calls put there."""
     # a convolution: dL/dI, dC^T fp32 and dx^T fp32 of every window row
