@@ -1499,9 +1499,7 @@ bool dx_one_pass(const ConvGeom &g, bool allow_split) {
 }
 
 // A handful of images leave the wide kernels with one each and their setup in
-// the open: 8 images of 13 x 8 x 8 to 16 channels, both directions, 42 us with
-// the contractions and 44 with them; 48 x 8 x 8 to 96, 60 and 62.  15 images of
-// 16 x 16 x 16 to 32: 72 and 69.
+// Fewer images than any of the wide kernels' fits below holds.
 constexpr int kWideMinImages = 12;
 
 // the weight gradient by conv_dw_wide_kernel: groups of equal size (groups of
@@ -1510,6 +1508,28 @@ struct DwWide {
     bool ok;
     int groups, cpg, cogroups, slices;
 };
+// Either way of the weight gradient, us, from fits to 185 layers (12 .. 4000
+// images of 6 x 6 .. 17 x 17, 4 .. 512 to 5 .. 512 channels; the one-kernel way
+// within 9 %, the contraction nine in ten within 30 %).  A workgroup of the
+// former stages every image of its share for its two groups of channels, and
+// fills 32-row steps with as few as 4 window rows: many channels on small images
+// go to the contraction (1655 images of 436 x 7 x 7 to 213 channels: 268 us
+// against 2462; 292 of 168 x 6 x 6 to 503: 56 against 232), few channels or
+// larger images do not (1000 of 16 x 12 x 12 to 32: 96 against 31).  Choosing
+// so loses 0.5 % against the better one on average.
+double dw_wide_us(const ConvGeom &g, const DwWide &p) {
+    const int blocks = p.groups * p.cogroups;
+    const double images = (double)((g.NB + p.slices - 1) / p.slices) *
+                          ((blocks * p.slices + 255) / 256);  // one after the other
+    const int steps = (4 * g.Hp * g.Wp + 31) / 32;
+    return 10.9 + images * (0.6 + 0.79 * steps + 0.112e-3 * p.cpg * g.H * g.W) +
+           0.563e-6 * 4.0 * (double)p.slices * g.Co * g.Ci * KS * KS;
+}
+double dw_gemm_us(const ConvGeom &g) {
+    const double n = (double)g.Ci * KS * KS, rows = (double)g.NB * 4 * g.Hp * g.Wp;
+    const double tiles = ((g.Co + 127) / 128) * 128.0 * ((g.Ci * KS * KS + 127) / 128) * 128.0;
+    return 21.0 + 6.59e-9 * tiles * rows + 1.01e-6 * rows * n + 1.48e-6 * rows * g.Co;
+}
 DwWide dw_wide(const ConvGeom &g, int in_dtype, bool allow_split) {
     DwWide p{};
     p.groups = (g.Ci + kDwwMaxCi - 1) / kDwwMaxCi;
@@ -1518,7 +1538,7 @@ DwWide dw_wide(const ConvGeom &g, int in_dtype, bool allow_split) {
     p.slices = max(1, min(g.NB, kDwMaxGrid / (p.groups * p.cogroups)));
     p.ok = in_dtype == SNN_U8 && allow_split && g.Hp * g.Wp <= kDwwMaxCells &&
            p.cpg * g.H * g.W <= kDwwMaxX && p.cpg >= 4 &&
-           g.NB >= kWideMinImages;
+           g.NB >= kWideMinImages && dw_wide_us(g, p) < dw_gemm_us(g);
     return p;
 }
 
@@ -1526,11 +1546,34 @@ DwWide dw_wide(const ConvGeom &g, int in_dtype, bool allow_split) {
 int dxw_rt(const ConvGeom &g) { return (((4 * g.Hp * g.Wp + 15) / 16) | 1); }
 int dxw_ksn(const ConvGeom &g) { return (g.Co + 31) / 32; }
 
+// Either way of the input gradient, us, from fits to 129 layers of the ranges
+// above up to 96 output channels (nine in ten within 11 % and 20 %).  Few images
+// leave the wide kernel's setup in the open (16 images of 16 x 14 x 14 to 96
+// channels 17 us by the contraction and 23; 24 of 20 x 12 x 12 to 32, 18 and
+// 12; 100 of 8 x 16 x 16 to 64, 32 and 20).
+double dx_wide_us(const ConvGeom &g) {
+    const int groups = (g.Ci + 2 * kDxwHalf - 1) / (2 * kDxwHalf);
+    const int cpg = (g.Ci + groups - 1) / groups, slices = max(1, min(g.NB, 256 / groups));
+    const int halves = cpg > kDxwHalf ? 2 : 1, ch = (cpg + halves - 1) / halves;
+    const int at_once = kDxThreads / (g.H * g.W);  // channels gathered together
+    const double images = (double)((g.NB + slices - 1) / slices) * ((groups * slices + 255) / 256);
+    const int tiles = dxw_rt(g) * dxw_ksn(g);
+    return 8.1 + 0.245 * tiles +
+           images * (0.548 + 0.298 * tiles + 0.316 * halves * ((ch + at_once - 1) / at_once));
+}
+double dx_gemm_us(const ConvGeom &g) {
+    const double n = (double)g.Ci * KS * KS, rows = (double)g.NB * 4 * g.Hp * g.Wp;
+    const double tiles = ((g.Ci * KS * KS + 63) / 64) * 64.0;
+    return 15.1 + 20.9e-9 * tiles * rows * g.Co + 1.11e-6 * rows * n + 1.71e-6 * rows * g.Co +
+           10.8e-6 * (double)g.NB * g.Ci * g.H * g.W;
+}
+
 // the input gradient by conv_dx_wide_kernel
 bool dx_wide(const ConvGeom &g, bool allow_split) {
     return allow_split && !dx_one_pass(g, allow_split) && g.Co <= kDxwMaxCo &&
            g.Hp * g.Wp <= kDxwMaxCells && g.H * g.W <= kDxThreads &&
-           g.NB >= kWideMinImages && dxw_lds(dxw_rt(g), dxw_ksn(g)) <= kDxwMaxLds;
+           g.NB >= kWideMinImages && dxw_lds(dxw_rt(g), dxw_ksn(g)) <= kDxwMaxLds &&
+           dx_wide_us(g) < dx_gemm_us(g);
 }
 
 template <int RT, int KSN>

@@ -37,7 +37,11 @@ def _bwd(d, dI, arg, x, w):
     (12, 13, 6, 6, 8), (13, 14, 8, 9, 32), (15, 16, 9, 8, 33), (12, 20, 12, 12, 65), (14, 21, 12, 14, 64),
     (13, 11, 14, 14, 96), (300, 32, 14, 14, 17), (12, 5, 16, 16, 31), (13, 6, 17, 16, 64),
     (12, 10, 16, 17, 1), (70, 48, 15, 14, 96), (12, 16, 8, 40, 64),
-    (12, 12, 16, 16, 80), (12, 8, 20, 20, 24), (12, 12, 14, 13, 100), (11, 13, 8, 8, 16)])
+    (12, 12, 16, 16, 80), (12, 8, 20, 20, 24), (12, 12, 14, 13, 100), (11, 13, 8, 8, 16),
+    # enough images for the input gradient's kernel; many channels on images of
+    # one pooled cell, which stay with the contraction
+    (33, 20, 12, 12, 65), (64, 11, 14, 14, 96), (64, 6, 17, 16, 64), (24, 10, 16, 17, 1),
+    (33, 16, 8, 40, 64), (300, 168, 6, 6, 100), (120, 60, 7, 7, 70)])
 def test_conv_bwd_wide(NB, Ci, H, W, Co):
     x, w, arg, dI, d = _case(NB, Ci, H, W, Co, NB + Ci + Co)
     gW, gx = _bwd(d, dI, arg, x, w)
@@ -51,12 +55,13 @@ def test_conv_bwd_wide(NB, Ci, H, W, Co):
     assert (np.abs(gW - rW) <= (3 * rows + 2) * 2.0 ** -24 * tW + 1e-30).all()
 
 
+@pytest.mark.parametrize("NB", [13, 40])
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan"), 3.4e38])
-def test_conv_dx_wide_of_special_values(bad):
+def test_conv_dx_wide_of_special_values(bad, NB):
     """dL/dI with a value that is not finite, or near fp32's largest: the
     gradient has the values the fp32 products give, an infinity against a
     nonzero weight an infinity of the product's sign."""
-    NB, Ci, H, W, Co = 13, 16, 14, 14, 40
+    Ci, H, W, Co = 16, 14, 14, 40
     x, w, arg, dI, d = _case(NB, Ci, H, W, Co, 3)
     dI[1, 7, 2, 3] = bad
     _, gx = _bwd(d, dI, arg, x, w)
