@@ -1498,7 +1498,6 @@ bool dx_one_pass(const ConvGeom &g, bool allow_split) {
            g.Hp * g.Wp <= kDxMaxCells && g.H * g.W <= kDxThreads;
 }
 
-// A handful of images leave the wide kernels with one each and their setup in
 // Fewer images than any of the wide kernels' fits below holds.
 constexpr int kWideMinImages = 12;
 

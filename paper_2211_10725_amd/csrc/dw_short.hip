@@ -15,9 +15,10 @@
 // quarter of K each and add their sums in LDS, in order, instead of in a
 // second launch.  The price, every A value split by N / 64 workgroups, is
 // below 5 us of vector work at the largest size taken.
-//  128 x  500 x 1000 (rows, outputs, inputs) 19.4 -> 5.6 us; 800 x 1000 x 784
-// 32 (with its reduction) -> 24; 128 x 1000 x 3072 16 -> 17.  Layers: 300 rows
-// of 3000 to 1000 130 -> 116, 800 of 1000 to 1000 125 -> 104.
+// The call, 128 x 500 x 1000 (rows, outputs, inputs) 17.5 -> 9.4 us (on inputs
+// out of the caches 21.1 -> 8.2), 800 x 1000 x 784 32.9 -> 22.8 (31.7 -> 26.1),
+// 512 x 1000 x 1000 30.2 -> 15.1.  Layers: 300 rows of 3000 to 1000 130 -> 116,
+// 800 of 1000 to 1000 125 -> 104.
 #include "snn_internal.hpp"
 
 namespace snn {
@@ -126,6 +127,20 @@ bool dw_short_applies(const GemmArgs &g) {
     // 64 x 64 by far; at 8 rows of 3000 x 3000 (77 against 86 us) the tiles'
     // sums and stores outweigh the product.
     if (g.K < 64 || g.K > 1024) return false;
+    // The 16-bit kernel is at its best with rows of B of whole 16 bytes.  There it
+    // splits outputs of at most 65536 elements over K further (1024 rows of 256 x
+    // 256 16.5 against 17.8 us, 800 rows 17.1 against 16.0).
+    const bool whole = g.ldb % 16 == 0;
+    if (whole && g.K > 896 && (int64_t)g.M * g.N <= 65536) return false;
+    // From 1024 tiles on (four workgroups per compute unit), splitting A once per
+    // 64 columns costs more than the barriers over few rows (64 of 2000 x 2000,
+    // 2016 tiles, 13.7 against 21.1 us; of 1500 x 1500 14.2 against 15.2), over
+    // more rows where the 16-bit kernel is at its best and from 1280 tiles (200
+    // rows of 2000 x 1000, 1024 tiles, 20.3 against 17.1; of 3072 x 1000, 1536,
+    // 23.0 against 23.5; of 2000 x 2000 24.0 against 29.6), else nowhere (100 rows
+    // of 3000 x 3000, 4418 tiles, 44.9 against 39.9).
+    const int64_t tiles = (int64_t)((g.M + kTM - 1) / kTM) * ((g.N + kTN - 1) / kTN);
+    if (tiles >= 1024 && (g.K < 96 || (whole && tiles >= 1280))) return false;
     // (above, the joint kernel takes the rest)
     return (double)g.M * g.N * g.K < 1073741824.0;
 }

@@ -11,7 +11,12 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,n_in,n_out", [(64, 64, 64), (65, 65, 97), (79, 784, 129), (128, 1000, 500),
                                           (129, 3072, 1000), (255, 191, 70), (800, 784, 1000),
                                           (1023, 333, 64), (1024, 64, 331), (63, 200, 300),
-                                          (1025, 200, 300)])
+                                          (1025, 200, 300),
+                                          # around the limits on small outputs and on tiles
+                                          (896, 256, 256), (897, 256, 256), (1000, 256, 264),
+                                          (64, 2048, 992), (64, 2000, 1024), (64, 2049, 1000),
+                                          (96, 2560, 1000), (95, 2560, 1000), (96, 2561, 1024),
+                                          (97, 2544, 1033)])
 def test_weight_gradient_of_few_rows(M, n_in, n_out):
     """Against the fp64 product: an fp32 sum of 3 M exact part products, in any
     order, is within (3 M + 2) 2^-24 of the sum of its terms' magnitudes."""
