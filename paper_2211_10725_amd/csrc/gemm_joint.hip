@@ -315,15 +315,45 @@ __device__ inline Item locate(const JointArgs &g, int it) {
     return r;
 }
 
-// A value of an operand from its parts (exact: hi + mid is, and adding lo
-// gives the fp32 value back)
-template <int P, bool MN>
-__device__ inline float whole(const uint16_t *X, int64_t ld, int64_t ps, int r, int k) {
-    const int64_t o = MN ? (int64_t)k * ld + r : (int64_t)r * ld + k;
-    float s = 0.f;
+// A 32 x 32 block of the product from the whole fp32 values of its operands'
+// parts (exact: hi + mid is, and adding lo gives the value back), A [row][k] and B
+// [k][row], on the fp32 matrix cores.  m, n: the lane's row and column
+// (clamped to ones that exist); lane half h takes k 8 h .. + 7 of each 16.
+__device__ inline float part_f32(uint32_t h) { return __uint_as_float(h << 16); }
+__device__ inline floatx16 whole_block(const uint16_t *A, int64_t lda,
+                                                          int64_t a_ps, const uint16_t *B,
+                                                          int64_t ldb, int64_t b_ps, int m, int n,
+                                                          int kbeg, int kend) {
+    const int h8 = 8 * ((threadIdx.x & 63) >> 5);
+    floatx16 t;
 #pragma unroll
-    for (int p = 0; p < P; ++p) s += __uint_as_float((uint32_t)X[p * ps + o] << 16);
-    return s;
+    for (int r = 0; r < 16; ++r) t[r] = 0.f;
+#pragma unroll 1
+    for (int k0 = kbeg; k0 < kend; k0 += 16) {
+        // (rows of A hold whole 16-byte chunks, k0 is a multiple of 16)
+        const int k = k0 + h8;
+        const uint16_t *a = A + (int64_t)m * lda + (k < kend ? k : 0);
+        u32x4 w[3];
+        uint32_t b[3][8];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p] = *reinterpret_cast<const u32x4 *>(a + p * a_ps);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[p][e] = B[p * b_ps + (int64_t)min(k + e, kend - 1) * ldb + n];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float x = 0.f, y = 0.f;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                x += part_f32((w[p][e / 2] >> (16 * (e & 1))) & 0xffffu);
+                y += part_f32(b[p][e]);
+            }
+            const bool in = k + e < kend;
+            t = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? x : 0.f, in ? y : 0.f, t, 0, 0, 0);
+        }
+    }
+    return t;
 }
 
 // two waves per SIMD: one workgroup of 8 waves, or two of 4 where their rings
@@ -584,25 +614,20 @@ void gemm_joint_kernel(JointArgs g) {
                 }
                 if constexpr (PA * PB == 9) {
                     // An infinity or NaN among the inputs leaves NaN against
-                    // zero parts: such a sum is taken again from the whole
+                    // zero parts: such a block is taken again from the whole
                     // values.
+                    static_assert(PA * PB != 9 || (LA == L_KC && LB == L_MN), "whole_block's layouts");
                     bool bad = false;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) bad |= !(__builtin_fabsf(v[r]) < INFINITY);
                     if (__builtin_expect(__any(bad), 0)) {
-#pragma unroll 1
-                        for (int r = 0; r < 16; ++r) {
-                            const int m = mb + 8 * (r >> 2) + (r & 3);
-                            float t = 0.f;
-                            if (m < g.M && n < g.N)
-                                for (int k = it.kbeg; k < it.kend; ++k)
-                                    t = __builtin_fmaf(
-                                        whole<PA, LA == L_MN>(g.A, g.lda, g.a_ps, m, k),
-                                        whole<PB, LB == L_MN>(g.B, g.ldb, g.b_ps, n, k), t);
+                        const int mf = it.m0 + (wm * FM + i) * 32 + (lane & 31);
+                        const floatx16 t =
+                            whole_block(g.A, g.lda, g.a_ps, g.B, g.ldb, g.b_ps, min(mf, g.M - 1),
+                                        min(n, g.N - 1), it.kbeg, it.kend);
 #pragma unroll
-                            for (int e = 0; e < 16; ++e)
-                                if (e == r && !(__builtin_fabsf(v[e]) < INFINITY)) v[e] = t;
-                        }
+                        for (int r = 0; r < 16; ++r)
+                            if (!(__builtin_fabsf(v[r]) < INFINITY)) v[r] = t[r];
                     }
                 }
                 float *row = Cz + (int64_t)mb * g.ldc + n;

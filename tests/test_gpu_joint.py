@@ -117,6 +117,25 @@ def test_input_gradient_of_special_values(bad, from_planes):
     assert bool(((gx.double() - ref.double()).abs()[fin] <= tol[fin]).all())
 
 
+@pytest.mark.parametrize("M,n_in,n_out", [(1600, 768, 1000), (2013, 1003, 1101), (300, 2048, 2056)])
+def test_input_gradient_of_a_diverged_step(M, n_in, n_out):
+    """Rows of dL/dI all NaN, all infinite, with one NaN or one infinity, among
+    finite ones: every block of the product has values to be taken again, and
+    the finite rows keep theirs."""
+    d, x, W, b, dI = _layer(M, n_in, n_out, False, 31)
+    W = W.abs() + 0.25  # an infinite row sums to an infinity
+    inf = float("inf")
+    dI[0::8], dI[1::8], dI[2::8, n_out - 1], dI[3::8, 17] = float("nan"), inf, -inf, float("nan")
+    ws = torch.empty(snn.snn_layer_workspace_bytes(d) + 256, dtype=torch.uint8, device="cuda")
+    gx = torch.empty((M, n_in), device="cuda")
+    snn.snn_synapse_bwd(d, dI, None, x, W, None, gx, ws)
+    assert bool(torch.isnan(gx[0::8]).all()) and bool(torch.isnan(gx[3::8]).all())
+    assert bool((gx[1::8] == inf).all()) and bool((gx[2::8] == -inf).all())
+    for r in range(4, 8):
+        rd, Wd = dI[r::8].double(), W.double()
+        _within(gx[r::8], rd @ Wd, rd.abs() @ Wd, 6 * n_out, 2.0 ** -26, "finite rows")
+
+
 @pytest.mark.parametrize("M", [64, 1600])
 def test_input_gradient_follows_dcur(M):
     """Of the stage call's two forms of dL/dI the weight gradient contracts
