@@ -815,23 +815,41 @@ __global__ __launch_bounds__(kDxThreads) void conv_dx_wide_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) bad |= !(__builtin_fabsf(acc[j][i][r]) < INFINITY);
             if (__builtin_expect(__any(bad), 0)) {
-#pragma unroll
-                for (int i = 0; i < RT; ++i)
+                // the same fragments as whole fp32 values, on the fp32 matrix
+                // cores (k index kg of element e: output channel 32 ks + 8 kg + e)
 #pragma unroll 1
-                    for (int r = 0; r < 4; ++r) {
-                        const int m = 16 * i + 4 * kg + r, q = m >> 2, d = m & 3;
-                        float t = 0.f;
-                        if (q < HW && cl < nch[j])
-                            for (int co = 0; co < Co; ++co) {
-                                const int o = nb * CHW + co * HW + q;
-                                t = __builtin_fmaf(arg[o] == d ? dI[o] : 0.f,
-                                                   w[co * Kc + (c0 + j * hc) * KS * KS + n], t);
-                            }
+                for (int i = 0; i < RT; ++i) {
+                    floatx4 t = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (e == r && !(__builtin_fabsf(acc[j][i][e]) < INFINITY))
-                                acc[j][i][e] = t;
+                    for (int ks = 0; ks < KSN; ++ks) {
+                        u32x4 ap[3], bp[3];
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            ap[p] = *reinterpret_cast<const u32x4 *>(
+                                dcp + p * PART + (16 * i + col) * LDC + 32 * ks + 8 * kg);
+                            bp[p] = bw[j][ks][p];
+                            // (the whole weights are not kept in registers over the rows)
+                            asm volatile("" : "+v"(bp[p]));
+                        }
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            float a = 0.f, b = 0.f;
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) {
+                                const int sh = 16 * (e & 1);
+                                a += __uint_as_float(((ap[p][e / 2] >> sh) & 0xffffu) << 16);
+                                b += __uint_as_float(((bp[p][e / 2] >> sh) & 0xffffu) << 16);
+                            }
+                            t = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, t, 0, 0, 0);
+                        }
                     }
+#pragma unroll
+                    for (int q = 0; q < RT; ++q)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (q == i && !(__builtin_fabsf(acc[j][q][r]) < INFINITY))
+                                acc[j][q][r] = t[r];
+                }
             }
         }
 #pragma unroll
