@@ -412,7 +412,8 @@ snn_status snn_neuron_fwd(const snn_layer_desc *d, const float *cur, const float
  * bf16(x - hi), lo = bf16(x - hi - mid)) for SNN_F32, else 1 plane of
  * d->grad_dtype (fp16 scaled as dcur); SNN_DCUR_T_PLANES, the same three
  * parts of an fp32 dL/dI as [3][T*B][n_out].  dcur may be NULL when dcur_t
- * is given. */
+ * is given.  An fp32 dcur may be the same pointer as cur or, for SNN_GRAD_FULL,
+ * as the gradient g (in place); any other overlap is undefined. */
 snn_status snn_neuron_bwd(const snn_layer_desc *d, const snn_grad_in *grad, const float *v,
                           const float *cur, const float *ckpt, void *dcur, void *dcur_t,
                           float *dcur_scale, float *grad_b, float *grad_v, void *ws,

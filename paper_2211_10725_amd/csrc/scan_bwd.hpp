@@ -129,11 +129,11 @@ struct FoldStage {
 // A chunk's loads are issued while the chunk after it runs, into the other of
 // two register sets.  The loads and stores of a whole chunk are free of
 // branches (addresses clamped to rows that exist, the lanes past the last
-// column repeating it): vector memory operations complete in order and the
-// compiler counts them, so a branch around one makes it wait for all of them,
-// stores included, once per chunk.  That wait bounded layers of few waves,
-// which leave nothing to run meanwhile (1000 steps of 65536 columns: 186 ->
-// 105 us; 101 recurrent steps of 25641: 19.9 -> 13.0 us).
+// column repeating it, in the wave that has it): vector memory operations
+// complete in order and the compiler counts them, so a branch around one makes
+// it wait for all of them, stores included, once per chunk.  That wait bounded
+// layers of few waves, which leave nothing to run meanwhile (1000 steps of 65536
+// columns: 186 -> 105 us; 101 recurrent steps of 25641: 19.9 -> 13.0 us).
 //
 // With TR = TR_TRANSPOSED, dL/dI is also written as the weight gradient's
 // operand: dcur_t [P][N][B*T] (P = 3 bf16 parts of fp32, else 1 plane of the
@@ -144,6 +144,12 @@ struct FoldStage {
 // TR = TR_PLANES (fp32 only), dcur_t holds the three bf16 parts in dcur's own
 // layout, [3][T][C], written at every step like dcur.  The row-major dcur
 // may be skipped (nullptr) in both cases.
+//
+// dcur may be cur or g itself: the value stored in a row follows from the values
+// loaded from it, a lane that repeats a column does both in the same instructions
+// as its owner, and a wave without columns does neither.  (The pointers stay
+// declared as if apart: without that, 1000 steps of 524288 columns take 1456
+// instead of 1428 us.)
 constexpr int TR_NONE = 0, TR_TRANSPOSED = 1, TR_PLANES = 2;
 template <int NEURON, int VEC, int GM, bool RESET_SURR, int GT, int TRM>
 __global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
@@ -165,6 +171,21 @@ __global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
     // (lanes past the last column repeat it, stores included)
     const int64_t col = lane_col < C ? lane_col : C - VEC;
     const int nch = (T + K - 1) / K, nck = nch - 1;
+    __shared__ __attribute__((aligned(16))) float frows[FOLD ? 2 : 1][FOLD ? Stage::kElems : 1];
+    const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+    if (((int64_t)blockIdx.x * kThreads + wave0) * VEC >= C) {
+        // no column: only the fold's staging, barrier for barrier as below
+        if constexpr (FOLD) {
+            const int64_t lo = ((int64_t)blockIdx.x * kThreads * VEC) / N;
+            Stage st;
+            for (int c = nck + 1; c >= 0; --c) {
+                st.load(fold, T, max(c - 1, 0) * K, lo);
+                st.store(frows[(c + 1) & 1], fold.dt_up);
+                __syncthreads();
+            }
+        }
+        return;
+    }
     float lam[VEC], lami[VEC], acc[VEC], gb[VEC], vr[VEC], dv[VEC], jump[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
@@ -176,7 +197,6 @@ __global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
     if constexpr (BCAST) Vec<VEC>::load(g + col, gb);
 
     // fold: the lane's columns of W_up, its batch row within the staged rows
-    __shared__ __attribute__((aligned(16))) float frows[FOLD ? 2 : 1][FOLD ? Stage::kElems : 1];
     float wcol[FOLD ? VEC : 1][FOLD ? KF : 1];
     int fbb = 0;
     int64_t b_lo = 0;
