@@ -1537,7 +1537,7 @@ struct DwWide {
 double dw_wide_us(const ConvGeom &g, const DwWide &p) {
     const int blocks = p.groups * p.cogroups;
     const double images = (double)((g.NB + p.slices - 1) / p.slices) *
-                          ((blocks * p.slices + 255) / 256);  // one after the other
+                          ((blocks * p.slices + kPlanCus - 1) / kPlanCus);  // one after the other
     const int steps = (4 * g.Hp * g.Wp + 31) / 32;
     return 10.9 + images * (0.6 + 0.79 * steps + 0.112e-3 * p.cpg * g.H * g.W) +
            0.563e-6 * 4.0 * (double)p.slices * g.Co * g.Ci * KS * KS;
@@ -1570,10 +1570,10 @@ int dxw_ksn(const ConvGeom &g) { return (g.Co + 31) / 32; }
 // 12; 100 of 8 x 16 x 16 to 64, 32 and 20).
 double dx_wide_us(const ConvGeom &g) {
     const int groups = (g.Ci + 2 * kDxwHalf - 1) / (2 * kDxwHalf);
-    const int cpg = (g.Ci + groups - 1) / groups, slices = max(1, min(g.NB, 256 / groups));
+    const int cpg = (g.Ci + groups - 1) / groups, slices = max(1, min(g.NB, kPlanCus / groups));
     const int halves = cpg > kDxwHalf ? 2 : 1, ch = (cpg + halves - 1) / halves;
     const int at_once = kDxThreads / (g.H * g.W);  // channels gathered together
-    const double images = (double)((g.NB + slices - 1) / slices) * ((groups * slices + 255) / 256);
+    const double images = (double)((g.NB + slices - 1) / slices) * ((groups * slices + kPlanCus - 1) / kPlanCus);
     const int tiles = dxw_rt(g) * dxw_ksn(g);
     return 8.1 + 0.245 * tiles +
            images * (0.548 + 0.298 * tiles + 0.316 * halves * ((ch + at_once - 1) / at_once));

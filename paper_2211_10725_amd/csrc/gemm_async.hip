@@ -604,7 +604,7 @@ AsyncPlan plan_async(const GemmArgs &g) {
     const int tiles = p.tiles_m * p.tiles_n;
     const int nk = (g.K + kKT - 1) / kKT;
     int S = 1;
-    const int cus = 256;  // one workgroup per CU; MI355X has 256 CUs
+    const int cus = kPlanCus;  // one workgroup each
     p.parts = planar(g.a_dtype) || planar(g.b_dtype) ? 3 : 1;
     if (tiles < cus) S = max(1, min(min(cus / tiles, p.parts * nk / 16), 64));
     const int per = (nk + S - 1) / S;
@@ -627,7 +627,7 @@ AsyncPlan plan_async(const GemmArgs &g) {
 // 256 ones leave compute units idle).
 double async_us(const GemmArgs &g, const AsyncPlan &p) {
     const int64_t items = (int64_t)p.tiles_m * p.tiles_n * p.splits;
-    double us = (double)((items + 255) / 256) * (p.k_chunk / kKT * 1.8 + 3.0);
+    double us = (double)((items + kPlanCus - 1) / kPlanCus) * (p.k_chunk / kKT * 1.8 + 3.0);
     if (p.splits > 1) us += 4.0 + (double)g.M * g.N * 4.0 * (2 * p.splits + 1) / 4.5e6;
     return us;
 }

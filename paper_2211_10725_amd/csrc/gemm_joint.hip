@@ -369,10 +369,10 @@ constexpr int waves_per_simd() {
 // added in turn, without writing the partials).
 //
 // The k-tiles of a workgroup's items, item after item, run through a ring of
-// R LDS slots; step t multiplies the tile in slot t % R.  With R >= 3, at the
+// R LDS slots; step t multiplies the tile in slot t % R.  With R = 3, at the
 // barrier that opens a step every wave has finished reading slot (t - 1) % R
 // and tile t + 1 has landed in every wave's view: the step issues the copies
-// of tile t + R - 1 into the slot just freed, and its last k16 step already
+// of tile t + 2 into the slot just freed, and its last k16 step already
 // reads tile t + 1's first fragments, so the matrix cores do not wait for
 // LDS reads across the barrier.  With R = 2 the barrier only gives tile t,
 // and the step copies tile t + 1.  The next item's first tiles are copied by
@@ -382,7 +382,8 @@ template <int MT, int PA, int PB, int LA, int LB, int BM, int BN, int KT, int R,
 __global__ __launch_bounds__(64 * WM * WN, (waves_per_simd<PA, PB, BM, BN, KT, R, WM * WN>()))
 void gemm_joint_kernel(JointArgs g) {
     constexpr int NW = WM * WN;
-    constexpr bool kCross = R >= 3;
+    static_assert(R == 2 || R == 3, "the waits below");
+    constexpr bool kCross = R == 3;
     using PR = Products<PA, PB>;
     using TA = Tile<LA, BM, KT, NW>;
     using TB = Tile<LB, BN, KT, NW>;
@@ -393,7 +394,6 @@ void gemm_joint_kernel(JointArgs g) {
     constexpr int NS = KT / 16;
     static_assert(NS % 2 == 0, "register sets alternate with the k16 steps of a tile");
     constexpr int NR = FA::kReads + FB::kReads, NM = FM * FN * PR::kCount;
-    constexpr int kCopies = PA * TA::kPer + PB * TB::kPer;  // per wave and tile
     constexpr int kStores = FM * FN * 16;                   // of a whole tile, per wave
     __shared__ __attribute__((aligned(1024))) char smem[R * kSlot];
     __shared__ __attribute__((aligned(16))) float sbias[2][BN];
@@ -428,7 +428,6 @@ void gemm_joint_kernel(JointArgs g) {
                                              (lds_void *)(&sbias[cj & 1][w * 64]), 4, 0, 0);
         }
     };
-    int ahead = 0;  // tiles copied or in flight that are not yet multiplied
     // the copies of one tile in three pieces, spread over a step's MFMAs
     auto copy_piece = [&](auto piece) {
         if (citem < 0) return;
@@ -443,7 +442,6 @@ void gemm_joint_kernel(JointArgs g) {
                 tb.copy(g.B + (p + (NP > 1 ? cplane : 0)) * g.b_ps, (uint32_t)g.ldb, g.b_cols, g.K, ck,
                         to + kOffB + p * TB::kPlane);
         } else {
-            ++ahead;
             cslot = cslot + 1 == R ? 0 : cslot + 1;
             ck += KT;
             if constexpr (NP > 1) {
@@ -473,8 +471,7 @@ void gemm_joint_kernel(JointArgs g) {
         static_for<0, 3>([&](auto piece) { copy_piece(piece); });
     if constexpr (kCross) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     int slot = 0;
-    int since_stores = 2;  // steps since a whole tile was stored
-    bool whole_tile_stored = false;
+    bool stored = false;  // a whole tile, just before this step
 
     for (int j = 0; item >= 0; ++j) {
         const Item it = locate<BM, BN>(g, item);
@@ -506,18 +503,15 @@ void gemm_joint_kernel(JointArgs g) {
                     }
                 }
             }
-            // The tile this barrier gives (t + 1, or t for R = 2) has landed;
-            // the tiles after it may be in flight.  A whole tile's stores were
-            // issued after every copy that the next steps wait for, and vector
-            // memory operations complete in order.
-            if (whole_tile_stored && since_stores < (kCross ? R - 2 : 1) && kStores >= 64)
+            // The tile this barrier gives (t + 1, or t for R = 2) has landed.
+            // A whole tile's stores may be in flight: they were issued after
+            // every copy that this step waits for, and vector memory
+            // operations complete in order.
+            if (stored && kStores >= 64)
                 asm volatile("s_waitcnt vmcnt(63)\n\ts_barrier" ::: "memory");
-            else if (R > 3 && ahead >= R - 1)
-                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(R > 3 ? (R - 3) * kCopies : 0)
-                             : "memory");
             else
                 asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-            ++since_stores;
+            stored = false;
             const int kvalid = it.kend - k0;
             const bool more = nk < it.kend;
             const uint32_t d = slot * kSlot;
@@ -562,7 +556,6 @@ void gemm_joint_kernel(JointArgs g) {
                 });
             });
             slot = ns;
-            --ahead;
             if (FOLD && chunk_done) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
@@ -599,8 +592,7 @@ void gemm_joint_kernel(JointArgs g) {
         }
         float *Cz = g.C + (int64_t)it.zk * g.split_stride;
         const bool full = it.m0 + BM <= g.M && it.n0 + BN <= g.N;
-        whole_tile_stored = full;
-        since_stores = 0;
+        stored = full;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -830,7 +822,7 @@ void plan_cfg(const GemmArgs &g, int cfg, JointPlan &best) {
     const int tm = (g.M + sh.BM - 1) / sh.BM, tn = (g.N + sh.BN - 1) / sh.BN;
     const int64_t tiles = (int64_t)tm * tn;
     const int nk = (g.K + sh.KT - 1) / sh.KT;
-    const int slots = 256 * sh.per_cu;  // MI355X has 256 CUs
+    const int slots = kPlanCus * sh.per_cu;
     for (int S = 1; S <= 32 && (S == 1 || nk / S >= 4); ++S) {
         const int per = (nk + S - 1) / S;
         const int splits = (nk + per - 1) / per;
@@ -879,7 +871,7 @@ SumOrder sum_order(const GemmArgs &g) {
 void plan_order(const GemmArgs &g, int cfg, bool fold, const SumOrder &o, JointPlan &best) {
     const Shape &sh = kShapes[cfg];
     const int tm = (g.M + sh.BM - 1) / sh.BM, tn = (g.N + sh.BN - 1) / sh.BN;
-    const int chunks = (g.K + o.chunk - 1) / o.chunk, slots = 256 * sh.per_cu;
+    const int chunks = (g.K + o.chunk - 1) / o.chunk, slots = kPlanCus * sh.per_cu;
     const int passes = o.turn ? 3 : 1;
     for (const int S : {1, chunks}) {
         if (S == 1 && chunks > 1 && (!fold || chunks >= 16)) continue;
@@ -1019,7 +1011,7 @@ bool faster(const GemmArgs &g) {
     }
     const double step = p.cfg == kThree ? 0.97 : p.cfg == kThreeSmall ? 0.56 : p.cfg == kThreeT ? 1.07
                         : p.cfg == kNineBig ? 2.5 : 1.34;
-    const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * p.splits + 255) / 256;
+    const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * p.splits + kPlanCus - 1) / kPlanCus;
     const int steps = ((p.splits > 1 ? p.k_chunk : g.K) + sh.KT - 1) / sh.KT;
     const double mb = (double)g.M * g.N * 4.0 * (p.splits > 1 ? 2 * p.splits + 2 : 1) / 1e6;
     auto packed = [](int t, double n) { return n * (t == SNN_F32 ? 10.0 : 3.0) / 1e6; };

@@ -68,6 +68,10 @@ __device__ inline void split_bf16x3(float x, uint32_t &hi, uint32_t &mid, uint32
     lo = bf16_rne_u32(r - __uint_as_float(mid << 16));
 }
 
+// Compute units that plans count on, MI355X's: a constant, so that neither a
+// workspace query nor an order of summation follows the current device (a
+// persistent grid does: device_cus()).
+constexpr int kPlanCus = 256;
 // Compute units of the current device (cached per device).
 int device_cus();
 
