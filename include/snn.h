@@ -119,11 +119,19 @@ typedef enum snn_status {
 
 /* descriptor flags */
 #define SNN_FLAG_FP32_MFMA 1 /* run every contraction on fp32 MFMA instead of
-                                exact multi-part passes on the 16-bit matrix
-                                cores (an fp32 operand split into hi + mid +
-                                lo bf16 parts, fp16 into two bf16 parts or
-                                kept as fp16; every product exact, fp32
-                                accumulate) */
+                                multi-part passes on the 16-bit matrix cores
+                                (an fp32 operand split into hi + mid + lo bf16
+                                parts, fp16 into two bf16 parts or kept as
+                                fp16; fp32 accumulate).  There, products of a
+                                spike or another 16-bit value with an fp32
+                                one are exact.  A product of two fp32 values
+                                (the input gradient from an fp32 dL/dI and
+                                fp32 weights, of large dense layers and of
+                                convolutions) is the sum of six of its nine
+                                part products, the three left out below 2^-26
+                                of it.  Parts below 2^-133, bf16's least
+                                value, are lost: a value below about 2^-110 is
+                                taken with an error of up to 2^-134 */
 
 /* losses on spike counts */
 #define SNN_LOSS_CE_COUNT 0  /* labels int32 [B] in [0,K) */
@@ -424,7 +432,7 @@ snn_status snn_neuron_bwd(const snn_layer_desc *d, const snn_grad_in *grad, cons
  * dcur_t (nullable): the operand snn_neuron_bwd wrote; the weight gradient
  * contracts it instead of transposing or splitting dcur (used when
  * snn_layer_dcur_t_bytes(d) > 0).  dcur may then be NULL unless grad_x is
- * requested.  dcur_scale: for SNN_F16, the scale snn_neuron_bwd wrote
+ * requested, which is always computed from dcur.  dcur_scale: for SNN_F16, the scale snn_neuron_bwd wrote
  * (required); the contractions divide it out.  Ignored for the other
  * dtypes. */
 snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void *dcur_t,
@@ -432,11 +440,11 @@ snn_status snn_synapse_bwd(const snn_layer_desc *d, const void *dcur, const void
                            const void *w, float *grad_w, float *grad_x, void *ws,
                            size_t ws_bytes, hipStream_t stream);
 
-/* Bytes of the transposed dL/dI operand (dcur_t of snn_neuron_bwd /
- * snn_synapse_bwd), or 0 when the layer's weight gradient does not take it
- * (conv layers, layers with at most 16 outputs, small products, and large
- * products of a 16-bit dL/dI, which read dL/dI and x in their own
- * layouts). */
+/* Bytes of the weight gradient's dL/dI operand (dcur_t of snn_neuron_bwd /
+ * snn_synapse_bwd), or 0 when the layer's weight gradient does not take one
+ * (conv layers, layers with at most 16 outputs, small products, and
+ * products that read dL/dI and x in their own layouts: of a large 16-bit
+ * dL/dI, and of an fp32 one over at most 8192 rows unless as planes). */
 size_t snn_layer_dcur_t_bytes(const snn_layer_desc *d);
 
 /* Layout of the dcur_t operand snn_neuron_bwd writes for this layer (-1 for
@@ -446,9 +454,10 @@ size_t snn_layer_dcur_t_bytes(const snn_layer_desc *d);
  * SNN_DCUR_T_PLANES: an fp32 dL/dI as its three exact bf16 parts (hi, mid,
  *   lo, as above) in dL/dI's own layout, [3][T*B][n_out], for a weight
  *   gradient that reads dL/dI untransposed (large dense fp32 layers whose
- *   n_out and n_in are multiples of 8).  snn_layer_bwd has the scan write
- *   these planes in place of the fp32 dL/dI when the layer has no input
- *   gradient to compute. */
+ *   n_out is a multiple of 8, where that is the faster way).  snn_layer_bwd
+ *   has the scan write these planes in place of the fp32 dL/dI unless the
+ *   layer has an input gradient to compute that does not contract them
+ *   too. */
 #define SNN_DCUR_T_TRANSPOSED 1
 #define SNN_DCUR_T_PLANES 2
 int32_t snn_layer_dcur_t_layout(const snn_layer_desc *d);

@@ -170,7 +170,7 @@ constexpr double kTransposeFlops = 1073741824.0;  // 2 M N K above which it pays
 
 struct DwPlan {
     bool transposed;
-    bool planes;       // fp32 dI as three bf16 planes in its own layout (asynchronous kernel)
+    bool planes;       // fp32 dI as three bf16 planes in its own layout
     int a_dtype;       // dtype of the transposed dI operand
     size_t dit_bytes;  // dI^T (planes for fp32)
     size_t xt_bytes;   // x^T
@@ -195,9 +195,11 @@ DwPlan dw_plan(const snn_layer_desc *d) {
     // transposed fragments (measured: 42 against 34 + 17 us of contraction and
     // transposes at 3200 rows, 127 against 85 + 34 us at 12800 rows).
     const bool mn_direct = d->grad_dtype == SNN_F32 && d->in_dtype == SNN_U8 && M <= 8192;
-    // A 16-bit dL/dI against 16-bit or spike x on the asynchronous pipeline:
-    // the tiles are staged M/N-contiguous as they are and read with
-    // transposing LDS loads, so no operand is transposed in global memory.
+    // The asynchronous and the joint kernel stage M/N-contiguous tiles as they
+    // are and read them with transposing LDS loads, so no operand is transposed
+    // in global memory: a 16-bit dL/dI against 16-bit or spike x, and an fp32 one
+    // against spikes as parts.  Over more than 8192 rows only outputs in whole
+    // 8s go that way.
     GemmArgs mn{};
     mn.M = d->n_out; mn.N = d->n_in; mn.K = M;
     mn.a_dtype = d->grad_dtype; mn.a_kc = false; mn.lda = d->n_out;
@@ -205,7 +207,8 @@ DwPlan dw_plan(const snn_layer_desc *d) {
     mn.allow_split = split_ok(d);
     const bool async_mn = gemm_async_applies(mn) ||
                           (gemm_joint_applies(mn) && (mn_direct || d->n_out % 8 == 0));
-    // (the scan's planes have dL/dI's own rows: whole 16-byte chunks)
+    // (the scan's planes have dL/dI's own rows, which the copies take in 16-byte
+    // chunks; other widths are split and padded by the contraction)
     p.planes = async_mn && d->grad_dtype == SNN_F32 && d->n_out % 8 == 0;
     p.transposed = split_ok(d) && gemm16_applies(kc) && d->n_out > 16 && !mn_direct && !async_mn &&
                    2.0 * M * d->n_in * d->n_out >= kTransposeFlops;

@@ -71,6 +71,27 @@ def test_products_of_one_term(M, n_in, n_out):
     assert bool(((gx.double() - ref).abs() <= 6 * 2.0 ** -24 * ref.abs()).all())
 
 
+@pytest.mark.parametrize("exp", [-100, -112, -124])
+def test_input_gradient_of_tiny_values(exp):
+    """dL/dI so small that its low parts are below bf16's least value: each value
+    is taken with an error of at most 2^-134."""
+    M, n_in, n_out = 1600, 768, 1000
+    g = _gen(-exp)
+    d = _desc(M, n_in, n_out)
+    W = _full_parts((n_out, n_in), g)
+    rows = torch.arange(M, device=DEV)
+    hot = torch.randint(0, n_out, (M,), generator=g, device=DEV)
+    v = (_full_parts((M,), g).double() * 2.0 ** exp).float()
+    one = torch.zeros((M, n_out), device=DEV)
+    one[rows, hot] = v
+    gx = torch.full((M, n_in), float("nan"), device=DEV)
+    snn.snn_synapse_bwd(d, one, None, None, W, None, gx, _ws(d))
+    ref = v.double()[:, None] * W[hot].double()
+    # (and six products rounded to fp32's least value)
+    bound = 6 * 2.0 ** -24 * ref.abs() + 2.0 ** -134 * W[hot].double().abs() + 6 * 2.0 ** -149
+    assert bool(((gx.double() - ref).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("M,n_in,n_out", [(6400, 1000, 1000), (1600, 768, 1000), (10715, 578, 96)])
 def test_layer_gradients_of_one_term(M, n_in, n_out):
     """The same through the layer call, whose scan writes the parts itself where
