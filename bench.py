@@ -45,10 +45,12 @@ SCAN_WORKLOAD = "scan_wide_t1000_b64"
 # kernel sources behind each kind of stage (a stored counter profile of a
 # stage stays valid while these files are unchanged)
 STAGE_SOURCES = {
-    "synapse": ["snn_internal.hpp", "gemm.hip", "gemm_mfma16.hip", "gemm_async.hip", "skinny.hip"],
-    "conv": ["snn_internal.hpp", "gemm.hip", "gemm_mfma16.hip", "gemm_async.hip", "skinny.hip",
-             "conv.hip"],
-    "neuron": ["snn_internal.hpp", "neuron.hpp", "scan.hip"],
+    "synapse": ["snn_internal.hpp", "gemm.hip", "gemm_mfma16.hip", "gemm_async.hip",
+                "gemm_joint.hip", "skinny.hip", "dw_short.hip"],
+    "conv": ["snn_internal.hpp", "gemm.hip", "gemm_mfma16.hip", "gemm_async.hip",
+             "gemm_joint.hip", "skinny.hip", "conv.hip"],
+    "neuron": ["snn_internal.hpp", "neuron.hpp", "scan_common.hpp", "scan.hip", "scan_bwd.hpp",
+               "scan_bwd_leaky.hip", "scan_bwd_synaptic.hip", "scan_bwd_rleaky.hip"],
 }
 
 
@@ -727,8 +729,27 @@ def _async_passes(a, b, M, N, K, mn=False):
 
 
 def _joint_ok(M, N, K):
-    """Mirrors gemm_joint_applies in gemm_joint.hip for fp32 operands."""
-    return M >= 64 and N >= 64 and K >= 192 and M * N * K >= 2 ** 30
+    """Sizes of fp32 by fp32 products that gemm_joint.hip takes (of narrow ones
+    only those it estimates to be faster)."""
+    return min(M, N) >= 128 and K >= 192 and M * N * K >= 2 ** 30
+
+
+def _joint_dw(d):
+    """The library's own answer for an fp32 weight gradient against spikes: its
+    dL/dI operand is planes where the parts are staged together."""
+    import paper_2211_10725_amd as snn
+    return d.synapse == 0 and snn.snn_layer_dcur_t_layout(d) == snn.DCUR_T_PLANES
+
+
+def _short_dw(d):
+    """Mirrors dw_short_applies in dw_short.hip."""
+    M, tiles = d.T * d.B, -(-d.n_out // 32) * -(-d.n_in // 64)
+    whole = d.n_in % 16 == 0
+    if min(d.n_out, d.n_in) < 64 or not 64 <= M <= 1024 or M * d.n_in * d.n_out >= 2 ** 30:
+        return False
+    if whole and M > 896 and d.n_in * d.n_out <= 65536:
+        return False
+    return tiles < 1024 or (M >= 96 and not (whole and tiles >= 1280))
 
 
 def _async_ok(a, b, M, N, K, mn=False):
@@ -763,11 +784,9 @@ def _stage_kernels(net, name, li, fp32_mfma):
                 return ": few_rows_mfma_kernel / few_rows_kernel + splitk_reduce_kernel"
             # mirrors dw_plan in api.hip
             sfx = f" ({passes} pass{'es' if passes > 1 else ''}, + splitk_reduce_kernel when split over K)"
-            if (not fp32_mfma and d.grad_dtype == 0 and d.in_dtype in (2, 3) and
-                    _joint_ok(d.n_out, d.n_in, M)):
+            if not fp32_mfma and d.grad_dtype == 0 and d.in_dtype in (2, 3) and _joint_dw(d):
                 return f": pack_kernel + gemm_joint_kernel{sfx}"
-            if (not fp32_mfma and d.grad_dtype == 0 and d.in_dtype == 3 and d.n_out >= 64 and
-                    d.n_in >= 64 and 64 <= M <= 1024):
+            if not fp32_mfma and d.grad_dtype == 0 and d.in_dtype == 3 and _short_dw(d):
                 return ": dw_short_kernel (3 passes)"
             if (not fp32_mfma and d.synapse == 0 and
                     _async_ok(d.grad_dtype, d.in_dtype, d.n_out, d.n_in, M, mn=True)):

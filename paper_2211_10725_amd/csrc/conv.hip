@@ -657,9 +657,9 @@ __global__ __launch_bounds__(kDxThreads) void conv_dx_kernel(
 // pipe in the gather; the two alternate in each workgroup, one per compute
 // unit.  The contraction and gather through HBM that it replaces moved 4 bytes
 // x 25 x Ci per window row both ways and ran the products on fp32 MFMA.
-// 1600 images of 32 x 14 x 14 to 64 channels: 452 -> 182 us (the products of
+// 1600 images of 32 x 14 x 14 to 64 channels: 439 -> 162 us (the products of
 // full tiles would take about 70 at the contractions' rate); 2400 of 48 x 9 x 9 to
-// 16, forward and both gradients 358 -> 252 us.
+// 16: 163 -> 91 us.
 constexpr int kDxwMaxCells = 36;
 constexpr int kDxwMaxCo = 96;
 constexpr int kDxwHalf = 5;                     // channels of a half: 125 of 128 columns
@@ -1096,7 +1096,8 @@ __global__ __launch_bounds__(kDxThreads) void conv_dw_kernel(
 // What bounds it: the matrix cores (three exact passes) and, about equally, the
 // LDS reads that gather the columns from the image.  col^T and the planes of
 // dC^T through HBM, which it replaces, cost as much as the contraction:
-// 1600 images of 32 x 14 x 14 to 64 channels 215 -> 102 us with the reduction.
+// 1600 images of 32 x 14 x 14 to 64 channels 198 -> 96 us with the reduction,
+// 2400 of 48 x 9 x 9 to 16 111 -> 68.
 constexpr int kDwwMaxCells = 36;
 constexpr int kDwwMaxCi = 12;
 constexpr int kDwwRows = 160;               // window rows: 5 steps of 32

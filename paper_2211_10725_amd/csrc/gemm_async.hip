@@ -666,7 +666,7 @@ bool gemm_async_applies(const GemmArgs &g) {
     if (!takes_async(g)) return false;
     const AsyncPlan p = plan_async(g);
     // three passes: the joint kernel stages the parts together (layer of 1000 to
-    // 1000 over 6400 rows 53 against 87 us forward), where it takes the product
+    // 1000 over 6400 rows 63 against 84 us forward), where it takes the product
     if (p.parts > 1) return !gemm_joint_applies(g);
     return async_us(g, p) <= gemm_joint_us(g);
 }

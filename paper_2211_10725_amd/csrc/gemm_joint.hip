@@ -21,13 +21,14 @@
 // measurable.  So all parts of a k-tile are staged at once: a spike tile is
 // copied once for three MFMAs per fragment, and every copy instruction should
 // touch whole 128-byte lines: operands that are rewritten anyway go in
-// fragment order, 1 KiB of consecutive memory per copy.  Measured, contraction
-// with its rewriting (before: the 16-bit kernel, the 256 x 256 kernel with its
-// planes in turn, or fp32 MFMA):
-//    6400 x 1000 x 1000  fp32 forward 87 -> 66 us, dx 189 -> 111 us
-//    2013 x 1003 x 1101  fp32 forward 96 -> 34, dW 65 -> 41, dx 87 -> 53 us
-//    6400 x 1000 x 1000  fp16 forward 37 -> 26, dW 44 -> 32, dx 43 -> 27 us
-//    5000 x 1500 x  700  fp16 forward 118 -> 42, dW 64 -> 47, dx 121 -> 33 us
+// fragment order, 1 KiB of consecutive memory per copy.  Measured, stage calls
+// with their rewriting and reductions (before: the 16-bit kernel, the 256 x 256
+// kernel with its planes in turn, or fp32 MFMA), rows x inputs x outputs:
+//    6400 x 1000 x 1000  fp32 forward 84 -> 63, dW 85 -> 70, dx 181 -> 106 us
+//    2013 x 1003 x 1101  fp32 forward 95 -> 37, dW 65 -> 39, dx  88 ->  52 us
+//    5000 x  700 x 1500  fp32 forward 150 -> 42, dW 107 -> 61, dx 147 -> 86 us
+//    6400 x 1000 x 1000  fp16 forward 39 -> 27, dW 46 -> 32, dx  45 ->  27 us
+//    2013 x 1003 x 1101  fp16 forward 91 -> 30, dW 102 -> 48, dx 133 -> 31 us
 //
 // A workgroup copies k-tiles of KT straight from global memory into a ring of
 // LDS slots (global_load_lds_dwordx4: lane i of a wave writes the 16 bytes at
@@ -967,11 +968,11 @@ namespace {
 // nine in ten within 12 %).  Tiles half empty, few rows or narrow layers and
 // deep splits go to the others: us, other kernel / this one,
 //   fp32 currents   64 rows 8192 -> 2048  30 / 59,  10715 rows 5776 -> 96  78 / 111
-//                   (6400 rows 1000 -> 1000  87 / 53,  2013 rows 1003 -> 1101  96 / 39)
+//                   (6400 rows 1000 -> 1000  84 / 63,  2013 rows 1003 -> 1101  95 / 37)
 //   fp32 dW         262144 rows 64 -> 64  78 / 293,  4096 rows 64 -> 4096  29 / 59
-//                   (2013 rows 1003 -> 1101  65 / 41,  3000 rows 600 -> 600  42 / 31)
+//                   (2013 rows 1003 -> 1101  65 / 39,  3000 rows 600 -> 600  42 / 31)
 //   fp32 dx         64 rows 8192 <- 2048  38 / 59,  16384 rows 64 <- 1024  50 / 62
-//                   (6400 rows 1000 <- 1000  189 / 122)
+//                   (6400 rows 1000 <- 1000  181 / 106)
 // Choosing so loses 0.5 % against the better one on average.
 bool faster(const GemmArgs &g) {
     GemmArgs o = g;
