@@ -821,14 +821,15 @@ struct JointPlan {
 void plan_cfg(const GemmArgs &g, int cfg, JointPlan &best) {
     const Shape &sh = kShapes[cfg];
     const int tm = (g.M + sh.BM - 1) / sh.BM, tn = (g.N + sh.BN - 1) / sh.BN;
-    const int64_t tiles = (int64_t)tm * tn;
+    const double tiles = (double)tm * tn;
     const int nk = (g.K + sh.KT - 1) / sh.KT;
-    const int slots = kPlanCus * sh.per_cu;
-    for (int S = 1; S <= 32 && (S == 1 || nk / S >= 4); ++S) {
+    // (host time: no 64-bit division in this loop, which several plans of a
+    // layer call run)
+    const double per_round = 1.0 / (kPlanCus * sh.per_cu);
+    for (int S = 1; S <= 32 && (S == 1 || 4 * S <= nk); ++S) {
         const int per = (nk + S - 1) / S;
-        const int splits = (nk + per - 1) / per;
-        if (splits != S) continue;
-        const int64_t rounds = (tiles * S + slots - 1) / slots;
+        if ((S - 1) * per >= nk) continue;  // fewer splits than S
+        const double rounds = __builtin_ceil(tiles * S * per_round);
         // an item: its steps and about 3 us of first copies and stores; split
         // partials are written and read once more at the copy rate
         double us = rounds * (per * (double)sh.step_us + 3.0);
