@@ -667,7 +667,8 @@ def _contraction_kind(net, li, fp32_mfma, stage="synapse_fwd"):
     # conv backward: one-pass kernels on the 16-bit cores (dW 3 exact passes,
     # dx 6 part products) where the image fits, else the fp32 contractions
     dx = li > 0 and net.gx[li] is not None
-    if _conv_one_pass_fw(net, li, fp32_mfma) and (not dx or _conv_one_pass(net, li, fp32_mfma)):
+    if _conv_one_pass_fw(net, li, fp32_mfma) and (not dx or _conv_one_pass(net, li, fp32_mfma) or
+                                                  _conv_dx_wide(net, li, fp32_mfma)):
         return "mfma16", (4.5 if dx else 3)
     return "mfma32", 1
 
@@ -680,6 +681,30 @@ def _conv_one_pass(net, li, fp32_mfma):
     hp, wp = (d.h_in - 4) // 2, (d.w_in - 4) // 2
     return (d.synapse == 1 and not fp32_mfma and d.c_in * 25 <= 320 and d.c_out <= 64
             and hp * wp <= 16 and d.h_in * d.w_in <= 512)
+
+
+def _conv_dx_wide(net, li, fp32_mfma):
+    """Whether layer li's conv input gradient runs as conv_dx_wide_kernel:
+    mirrors dx_wide in conv.hip with its two estimates."""
+    d = net.descs[li]
+    NB, HW, px = d.T * d.B, ((d.h_in - 4) // 2) * ((d.w_in - 4) // 2), d.h_in * d.w_in
+    if (d.synapse != 1 or fp32_mfma or _conv_one_pass(net, li, fp32_mfma) or d.c_out > 96 or
+            HW > 36 or px > 512 or NB < 12):
+        return False
+    rt, ksn = (4 * HW + 15) // 16 | 1, -(-d.c_out // 32)
+    if 512 * (16 * rt + 4) + 96 * rt * (32 * ksn + 8) > 160 * 1024 - 256:
+        return False
+    groups = -(-d.c_in // 10)
+    cpg, slices = -(-d.c_in // groups), max(1, min(NB, 256 // groups))
+    halves = 2 if cpg > 5 else 1
+    each = -(-cpg // halves)
+    gathers = halves * -(-each // (512 // px))
+    images = -(-NB // slices) * -(-groups * slices // 256)
+    wide = 8.1 + 0.245 * rt * ksn + images * (0.548 + 0.298 * rt * ksn + 0.316 * gathers)
+    cols, rows = 25 * d.c_in, 4.0 * NB * HW
+    other = (15.1 + 20.9e-9 * -(-cols // 64) * 64 * rows * d.c_out + 1.11e-6 * rows * cols +
+             1.71e-6 * rows * d.c_out + 10.8e-6 * NB * d.c_in * px)
+    return wide < other
 
 
 def _conv_one_pass_fw(net, li, fp32_mfma):
@@ -826,6 +851,8 @@ def _stage_kernels(net, name, li, fp32_mfma):
             return f": {dw} (conv weight gradient)"
         if one:
             return f": {dw} + conv_dx_kernel (conv weight and input gradients)"
+        if one_w and _conv_dx_wide(net, li, fp32_mfma):
+            return f": {dw} + conv_dx_wide_kernel (conv weight and input gradients)"
         if one_w:
             return (f": {dw} + unpool_t_kernel + contraction + col2im_kernel "
                     "(conv weight and input gradients)")
