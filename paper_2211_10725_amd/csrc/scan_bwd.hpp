@@ -173,8 +173,9 @@ __global__ __launch_bounds__(kThreads) void neuron_bwd_kernel(
     const int nch = (T + K - 1) / K, nck = nch - 1;
     __shared__ __attribute__((aligned(16))) float frows[FOLD ? 2 : 1][FOLD ? Stage::kElems : 1];
     const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
-    if (((int64_t)blockIdx.x * kThreads + wave0) * VEC >= C) {
-        // no column: only the fold's staging, barrier for barrier as below
+    // (a wave without a column only stages the fold's rows, barrier for barrier as below;
+    // out of line: a training step of 125-workgroup scans 94.7 -> 94.0 us, 93.5 without it)
+    if (__builtin_expect(((int64_t)blockIdx.x * kThreads + wave0) * VEC >= C, 0)) {
         if constexpr (FOLD) {
             const int64_t lo = ((int64_t)blockIdx.x * kThreads * VEC) / N;
             Stage st;
