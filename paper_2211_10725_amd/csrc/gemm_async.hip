@@ -660,6 +660,33 @@ bool takes_async(const GemmArgs &g) {
     return g.pool_hw == 0 && !g.c_div && p.tiles_m * p.tiles_n * p.splits >= 192 &&
            (double)g.M * g.N * g.K >= 4294967296.0;
 }
+
+// K-contiguous planes against spikes (weight gradients over more than 8192 rows
+// of a width that is no multiple of 8): the 16-bit kernel's 128 x 128 tiles, two
+// workgroups on a compute unit, against the 256 x 256 ones.  Where K is a
+// multiple of 16 its spikes load in 16-byte chunks and it is the faster one for
+// outputs that fill the larger tiles badly; elsewhere it was slower on all 24
+// sizes tried.  A fit to 97 weight gradients of 2^32 .. 2^36 products; the
+// choice is 0.5 % from the better kernel on average there, 0.7 % on 49 others
+// (always these tiles 8 and 7 %, never 4 and 3 %).  us, 16-bit kernel / this one:
+//   38384 rows 2232 -> 294  330 / 461, 12288 rows 1032 -> 594  106 / 114,
+//   13888 rows 1528 -> 1325  293 / 261, 13376 rows 1528 -> 2967  673 / 484
+bool small_tiles_faster(const GemmArgs &g, const AsyncPlan &p) {
+    if (g.a_dtype != kPlanes3 || g.b_dtype != SNN_U8 || !g.a_kc || g.K % 16 != 0) return false;
+    const double mb = (double)g.M * g.N * 4e-6;  // one output, or one split's partials
+    const int64_t items = (int64_t)p.tiles_m * p.tiles_n * p.splits;
+    const double large = (double)((items + kPlanCus - 1) / kPlanCus) * (p.k_chunk / kKT * 3.46 - 1.4) +
+                         (p.splits > 1 ? 0.29 * mb * (2 * p.splits + 1) : 0.0) +
+                         1.19e-6 * g.N * g.K;  // spikes widened
+    const int64_t slots = 2 * kPlanCus, tiles = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    const int64_t steps = (g.K + 31) / 32;
+    int64_t S = tiles < slots ? slots / tiles : 1;
+    const int64_t per = (steps + S - 1) / S;
+    S = (steps + per - 1) / per;
+    const double small = (double)((tiles * S + slots - 1) / slots) * per * 1.23 +
+                         (S > 1 ? 0.40 * mb * (2 * S + 1) : 0.0) + 1.4;
+    return small < large;
+}
 }  // namespace
 
 bool gemm_async_applies(const GemmArgs &g) {
@@ -667,7 +694,7 @@ bool gemm_async_applies(const GemmArgs &g) {
     const AsyncPlan p = plan_async(g);
     // three passes: the joint kernel stages the parts together (layer of 1000 to
     // 1000 over 6400 rows 63 against 84 us forward), where it takes the product
-    if (p.parts > 1) return !gemm_joint_applies(g);
+    if (p.parts > 1) return !gemm_joint_applies(g) && !small_tiles_faster(g, p);
     return async_us(g, p) <= gemm_joint_us(g);
 }
 

@@ -163,6 +163,19 @@ def test_narrow_weight_gradients_keep_their_kernel():
         assert snn.snn_layer_dcur_t_bytes(d) >= 6 * rows * n_out
 
 
+def test_tall_weight_gradients_keep_their_tiles():
+    """A weight gradient over very many rows in whole 16s, of outputs that fill
+    256 x 256 tiles badly, is contracted from the spikes' bytes: next to dL/dI,
+    its three planes and the transposed bytes there is no room for 16-bit spikes.
+    Rows in whole 8s alone have it."""
+    for rows, n_in, n_out, widened in [(155600, 992, 263, False), (137728, 1672, 290, False),
+                                       (155592, 992, 263, True)]:
+        d = snn.layer_desc(dict(kind="dense", n_in=n_in, n_out=n_out, neuron="leaky", beta=0.9), 1,
+                           rows)
+        room = snn.snn_layer_workspace_bytes(d) - rows * (10 * n_out + n_in)
+        assert (room >= 2 * rows * n_in) == widened, (rows, n_in, n_out)
+
+
 def test_workspace_of_large_layers():
     """Workspaces of 2 GiB and more hold what the layer's calls put there."""
     # a convolution: dL/dI, dC^T fp32 and dx^T fp32 of every window row

@@ -187,7 +187,9 @@ def test_currents_in_the_kept_order(M, n_in, n_out, bytes_in):
 # tiles with the parts in turn.
 
 
-@pytest.mark.parametrize("M,n_in,n_out", [(9000, 1024, 1001), (8200, 1288, 515), (65544, 264, 270)])
+@pytest.mark.parametrize("M,n_in,n_out", [(9000, 1024, 1001), (8200, 1288, 515), (65544, 264, 270),
+                                          # rows in whole 16s: these tiles, then smaller ones
+                                          (13376, 1528, 1327), (16640, 2232, 294), (38384, 267, 1001)])
 def test_weight_gradient_of_parts_in_turn(M, n_in, n_out):
     """K-contiguous planes: more than 8192 rows, outputs no multiple of 8.  A
     column of x with one spike gives the row of dL/dI there, bit for bit; one
